@@ -361,11 +361,29 @@ __global__ __launch_bounds__(kThreads) void prefill_gather(PrefillArgs a) {
   const T* Vr = reinterpret_cast<const T*>(L.base + sec.V) + unit * L.R * D;
   T* hk = static_cast<T*>(L.hk) + unit * a.Wcap * D;
   T* hv = static_cast<T*>(L.hv) + unit * a.Wcap * D;
-  for (int idx = blockIdx.x * kThreads + threadIdx.x; idx < n * D; idx += gridDim.x * kThreads) {
-    const int i = idx / D, c = idx - i * D;
-    const int32_t s = int32_t((sr.h0 + i) % L.R);
-    hk[int64_t(i) * D + c] = Kr[kring_elem(s, c, D)];
-    hv[int64_t(i) * D + c] = Vr[vring_elem(s, c, D)];
+  constexpr int CPR = D / 8;
+  const int stride = gridDim.x * kThreads;
+  // keys: a slot's row is made of 16-byte chunks (8 columns), moved whole
+  for (int idx = blockIdx.x * kThreads + threadIdx.x; idx < n * CPR; idx += stride) {
+    const int i = idx / CPR, ch = idx - i * CPR;
+    Frag<T> f;
+    f.load(Kr + kring_elem(int32_t((sr.h0 + i) % L.R), 8 * ch, D));
+    store8(hk + int64_t(i) * D + 8 * ch, f);
+  }
+  // values: the ring keeps 8 consecutive slots of one column together (R is a
+  // multiple of 8, so a group of 8 tokens never wraps): one 16-byte read per
+  // column, then one element of each of the 8 rows (consecutive lanes write
+  // consecutive columns)
+  const int64_t m0 = sr.h0 >> 3;
+  const int ng = int(((sr.p0 - 1) >> 3) - m0 + 1);
+  for (int idx = blockIdx.x * kThreads + threadIdx.x; idx < ng * D; idx += stride) {
+    const int gi = idx / D, c = idx - gi * D;
+    const int64_t j0 = (m0 + gi) * 8;
+    T x[8];
+    __builtin_memcpy(x, __builtin_assume_aligned(Vr + vring_elem(int32_t(j0 % L.R), c, D), 16), sizeof(x));
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      if (j0 + e >= sr.h0 && j0 + e < sr.p0) hv[(j0 + e - sr.h0) * D + c] = x[e];
   }
   if (a.gated) {  // the history tokens' G_j, from the gate ring
     const LayerSections sg = layer_sections(a.B, a.Hkv, D, DF, L.R, sizeof(T), true);
@@ -475,47 +493,40 @@ __global__ __launch_bounds__(kSegThreads) void prefill_segsum(PrefillArgs a) {
   // memory access.  New tokens' rows are Hkv * D elements apart; history
   // rows (a continuing prefill) are consecutive.
   const uint32_t rowb = uint32_t(a.Hkv) * D * sizeof(T);
-  const brsrc_t rkn = make_rsrc(sr.kin + (int64_t(sr.start) * a.Hkv + g) * D, uint32_t(a.seq_len[bl]) * rowb);
-  const brsrc_t rvn = make_rsrc(sr.vin + (int64_t(sr.start) * a.Hkv + g) * D, uint32_t(a.seq_len[bl]) * rowb);
+  const T* kn0 = sr.kin + (int64_t(sr.start) * a.Hkv + g) * D;  // this KV head's first new row
+  const T* vn0 = sr.vin + (int64_t(sr.start) * a.Hkv + g) * D;
   const int nhist = int(sr.p0 - sr.h0);
-  const brsrc_t rkh = make_rsrc(sr.kh, uint32_t(nhist) * D * sizeof(T));
-  const brsrc_t rvh = make_rsrc(sr.vh, uint32_t(nhist) * D * sizeof(T));
-  // row j (absolute), byte cb of the row: its offset among the new rows
-  // and among the history rows (kOOB where it is not one, or not wanted)
-  auto offs = [&](int64_t j, uint32_t cb, bool ok, uint32_t& on, uint32_t& oh) {
-    const int jr = int(j - sr.p0);
-    on = ok && jr >= 0 ? uint32_t(jr) * rowb + cb : kOOB;
-    oh = ok && jr < 0 ? uint32_t(jr + nhist) * uint32_t(D * sizeof(T)) + cb : kOOB;
-  };
+  // A slab wholly among the history rows is read from them (base, size and
+  // row pitch picked in scalar registers: no wait here); a slab that holds
+  // rows of both kinds (one at most) reads both and merges them.
   auto load_slab = [&](int64_t j0) {
-    const bool hist = j0 < sr.p0;  // the slab reaches into the history rows (uniform)
-    {  // the lane's key row of the slab's key tile (phi_slab's A fragments)
-      const int64_t j = j0 + 16 * slab_key_tile<D, DF, kSegSlab>(kSegWaves) + hq;
-      kx.ok = j < jhi;
-#pragma unroll
-      for (int kk = 0; kk < D / 32; ++kk) {
-        uint32_t on, oh;
-        offs(j, uint32_t((32 * kk + 8 * lg) * sizeof(T)), kx.ok, on, oh);
-        bload_frag(kx.x[kk], rkn, on);
-        if (hist) {
-          Frag<T> h;
-          bload_frag(h, rkh, oh);
-          kx.x[kk] = frag_or(kx.x[kk], h);
-        }
+    const bool hist = j0 + kSegSlab - 1 < sr.p0;                // (uniform)
+    const bool mixed = !hist && j0 < sr.p0;
+    const T* kb = hist ? sr.kh : kn0;
+    const T* vb = hist ? sr.vh : vn0;
+    const uint32_t hb = uint32_t(nhist) * D * sizeof(T);
+    const uint32_t nb = hist ? hb : uint32_t(a.seq_len[bl]) * rowb, rp = hist ? uint32_t(D * sizeof(T)) : rowb;
+    const int j1 = int(j0 - (hist ? sr.h0 : sr.p0));  // the slab's first key, relative to its rows' first
+    auto row = [&](Frag<T>& f, const T* base, const T* hbase, int r, uint32_t cb, bool ok) {
+      const int jr = j1 + r;
+      bload_frag(f, make_rsrc(base, nb), ok && jr >= 0 ? uint32_t(jr) * rp + cb : kOOB);
+      if (mixed) {
+        Frag<T> h;
+        bload_frag(h, make_rsrc(hbase, hb), ok && jr < 0 ? uint32_t(jr + nhist) * uint32_t(D * sizeof(T)) + cb : kOOB);
+        f = frag_or(f, h);
       }
+    };
+    {  // the lane's key row of the slab's key tile (phi_slab's A fragments)
+      const int r = 16 * slab_key_tile<D, DF, kSegSlab>(kSegWaves) + hq;
+      kx.ok = j0 + r < jhi;
+#pragma unroll
+      for (int kk = 0; kk < D / 32; ++kk) row(kx.x[kk], kb, sr.kh, r, uint32_t((32 * kk + 8 * lg) * sizeof(T)), kx.ok);
     }
 #pragma unroll
     for (int u = 0; u < VPT; ++u) {
       const int id = tid + u * kSegThreads, r = id / CPR, ch = id - r * CPR;
       vok[u] = j0 + r < jhi;
-      uint32_t on, oh;
-      offs(j0 + r, uint32_t(8 * sizeof(T)) * ch, vok[u], on, oh);
-      bload_frag(vx[u], rvn, on);
-      if (hist) {
-        Frag<T> h;
-        bload_frag(h, rvh, oh);
-        vx[u] = frag_or(vx[u], h);
-      }
+      row(vx[u], vb, sr.vh, r, uint32_t(8 * sizeof(T)) * ch, vok[u]);
     }
   };
   if (jlo < jhi) load_slab(jlo);
@@ -808,17 +819,22 @@ void prefill_main(PrefillArgs a) {
   const uint32_t hbytes = uint32_t(sr.p0 - sr.h0) * D * sizeof(T);  // the history rows
   auto load_slab = [&](int s0) {
     const int64_t jb = t0 - Wd + s0;  // the slab's first key (uniform)
+    const int jn = int(jb - sr.p0);
+    const bool hist = jn + SL - 1 < 0;      // wholly among the history rows (as in fetch below)
+    const T* kb = hist ? sr.kh : kn0;
+    const T* vb = hist ? sr.vh : vn0;
+    const uint32_t nb = hist ? hbytes : nbytes, rp = hist ? uint32_t(D * sizeof(T)) : rowb;
+    const int j1 = hist ? jn + int(sr.p0 - sr.h0) : jn;
 #pragma unroll
     for (int u = 0; u < VPT; ++u) {
       const int id = tid + u * NTH, r = id / CPR, ch = id - r * CPR;
-      const int64_t j = jb + r;
-      const bool ok = s0 + r < nk && j >= 0;
-      const int jr = int(j - sr.p0);  // key relative to the first new token
+      const bool ok = s0 + r < nk && jb + r >= 0;
+      const int jr = j1 + r;
       const uint32_t cb = uint32_t(8 * sizeof(T)) * ch;
-      const uint32_t on = ok && jr >= 0 ? uint32_t(jr) * rowb + cb : kOOB;
-      bload_frag(kst[u], make_rsrc(kn0, nbytes), on);
-      bload_frag(vst[u], make_rsrc(vn0, nbytes), on);
-      if (jb < sr.p0) {  // the slab reaches into the history rows
+      const uint32_t on = ok && jr >= 0 ? uint32_t(jr) * rp + cb : kOOB;
+      bload_frag(kst[u], make_rsrc(kb, nb), on);
+      bload_frag(vst[u], make_rsrc(vb, nb), on);
+      if (!hist && jn < 0) {  // the slab holds rows of both kinds
         const uint32_t oh = ok && jr < 0 ? uint32_t(jr + int(sr.p0 - sr.h0)) * uint32_t(D * sizeof(T)) + cb : kOOB;
         Frag<T> hk, hv;
         bload_frag(hk, make_rsrc(sr.kh, hbytes), oh);
@@ -852,25 +868,42 @@ void prefill_main(PrefillArgs a) {
     if (stager) {
       const int64_t jt = kb0 + 32 * int64_t(n);   // the tile's first key (uniform)
       const int lo = int(klo - jt), hi = int(khi - jt);
-      const T* kn = sr.kin + (int64_t(sr.start) * a.Hkv + g) * D;
-      const T* vn = sr.vin + (int64_t(sr.start) * a.Hkv + g) * D;
+      // (32-bit: a band starts at most W before the first new token)
+      const int jn = int(kb0 - sr.p0) + 32 * n, nh = int(sr.p0 - sr.h0);
+      // A tile wholly among the history rows is read from them alone.  Only a
+      // tile that holds rows of both kinds (one per pass at most) reads both
+      // and merges them, which waits for the loads here: done for every
+      // history tile it put the memory latency into each of them (8 sequences
+      // of 16K tokens extended by 301 .. 2047, W = 1000: 551 us per call
+      // against 450).
 #pragma unroll
       for (int u = 0; u < SPT; ++u) {
         const int id = tid + u * NTH, srr = id / CPR, sch = id - srr * CPR;
         const bool ok = srr >= lo && srr <= hi;
-        const int jr = int(jt - sr.p0) + srr;      // key relative to the first new token
         const uint32_t cb = uint32_t(8 * sizeof(T)) * sch;  // the thread's 8-element chunk of the row
-        const uint32_t on = ok && jr >= 0 ? uint32_t(jr) * rowb + cb : kOOB;
-        bload_frag(sk[u], make_rsrc(kn, nbytes), on);
-        bload_frag(sv[u], make_rsrc(vn, nbytes), on);
-        if (jt < sr.p0) {  // the tile reaches into the history rows
-          const uint32_t hb = uint32_t(sr.p0 - sr.h0) * D * sizeof(T);
-          const uint32_t oh = ok && jr < 0 ? uint32_t(jr + int(sr.p0 - sr.h0)) * uint32_t(D * sizeof(T)) + cb : kOOB;
-          Frag<T> hk, hv;
-          bload_frag(hk, make_rsrc(sr.kh, hb), oh);
-          bload_frag(hv, make_rsrc(sr.vh, hb), oh);
-          sk[u] = frag_or(sk[u], hk);
-          sv[u] = frag_or(sv[u], hv);
+        auto new_rows = [&](Frag<T>& fk, Frag<T>& fv) {
+          const int jr = jn + srr;                 // key relative to the first new token
+          const uint32_t on = ok && jr >= 0 ? uint32_t(jr) * rowb + cb : kOOB;
+          bload_frag(fk, make_rsrc(sr.kin + (int64_t(sr.start) * a.Hkv + g) * D, nbytes), on);
+          bload_frag(fv, make_rsrc(sr.vin + (int64_t(sr.start) * a.Hkv + g) * D, nbytes), on);
+        };
+        auto old_rows = [&](Frag<T>& fk, Frag<T>& fv) {
+          const uint32_t hb = uint32_t(nh) * D * sizeof(T);
+          const int jh = jn + nh + srr;            // key relative to the first history row
+          const uint32_t oh = ok && jh >= 0 && jh < nh ? uint32_t(jh) * uint32_t(D * sizeof(T)) + cb : kOOB;
+          bload_frag(fk, make_rsrc(sr.kh, hb), oh);
+          bload_frag(fv, make_rsrc(sr.vh, hb), oh);
+        };
+        if (jn + 31 < 0) {  // (uniform)
+          old_rows(sk[u], sv[u]);
+        } else {
+          new_rows(sk[u], sv[u]);
+          if (jn < 0) {
+            Frag<T> hk, hv;
+            old_rows(hk, hv);
+            sk[u] = frag_or(sk[u], hk);
+            sv[u] = frag_or(sv[u], hv);
+          }
         }
       }
     }
