@@ -444,6 +444,11 @@ __device__ __forceinline__ brsrc_t make_rsrc(const void* base, uint32_t bytes) {
 __device__ __forceinline__ uint4 bload16(brsrc_t r, uint32_t off) {
   return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
 }
+// A store at or beyond the size is dropped (offset kOOB: no branch around it).
+__device__ __forceinline__ void bstore16(brsrc_t r, uint32_t off, uint4 v) {
+  typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+  __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{v.x, v.y, v.z, v.w}, r, off, 0, 0);
+}
 __device__ __forceinline__ float4 bload_f4(brsrc_t r, uint32_t off) {
   return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
 }

@@ -196,6 +196,37 @@ __device__ __forceinline__ void store4(bf16_t* dst, f32x4_t x, float s) {
 __device__ __forceinline__ void store4(float* dst, f32x4_t x, float s) {
   *reinterpret_cast<float4*>(dst) = make_float4(x[0] * s, x[1] * s, x[2] * s, x[3] * s);
 }
+// The output tiles of one query row (value columns 16ct + 4lg .. +3 in lane
+// group lg's acc[ct]), scaled, to the row at byte offset `row` of a buffer
+// (kOOB: the row does not exist, nothing is written).  No branch: the number
+// of memory operations behind a load is then the same on every path, and the
+// wait for that load need not wait for these stores as well.
+//   bf16: a row swap between lane groups pairs two 4-column pieces, so that a
+//   lane stores 16 bytes and the row's 4 lanes 64 consecutive bytes (8-byte
+//   stores took twice the store instructions for 32-byte pieces).
+template <int CT>
+__device__ __forceinline__ void store_row(brsrc_t r, uint32_t row, const f32x4_t (&acc)[CT], float s, bf16_t) {
+  static_assert(CT % 2 == 0, "column tiles go in pairs");
+  const uint32_t lg = (threadIdx.x & 63) >> 4;
+  // even groups keep tile ct (their own columns and the next group's), odd
+  // groups take tile ct + 1 (the previous group's columns and their own)
+  const uint32_t o = row == kOOB ? kOOB : row + 2 * (16 * (lg & 1) + 4 * (lg & 2));
+#pragma unroll
+  for (int ct = 0; ct < CT; ct += 2) {
+    const auto p = __builtin_amdgcn_permlane16_swap(pack_bf16x2(acc[ct][0] * s, acc[ct][1] * s),
+                                                    pack_bf16x2(acc[ct + 1][0] * s, acc[ct + 1][1] * s), false, false);
+    const auto q = __builtin_amdgcn_permlane16_swap(pack_bf16x2(acc[ct][2] * s, acc[ct][3] * s),
+                                                    pack_bf16x2(acc[ct + 1][2] * s, acc[ct + 1][3] * s), false, false);
+    bstore16(r, o + 2 * 16 * ct, make_uint4(p[0], q[0], p[1], q[1]));
+  }
+}
+template <int CT>
+__device__ __forceinline__ void store_row(brsrc_t r, uint32_t row, const f32x4_t (&acc)[CT], float s, float) {
+  const uint32_t lg = (threadIdx.x & 63) >> 4;
+  const uint32_t o = row == kOOB ? kOOB : row + 4 * 4 * lg;
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct) bstore16(r, o + 4 * 16 * ct, __builtin_bit_cast(uint4, acc[ct] * s));
+}
 // dst[0..3] += x * s (the second pass of a hybrid-form prefill)
 __device__ __forceinline__ void add4(bf16_t* dst, f32x4_t x, float s) {
   const uint2 o = *reinterpret_cast<const uint2*>(dst);
@@ -814,6 +845,7 @@ void prefill_main(PrefillArgs a) {
   // consecutive.
   const uint32_t rowb = uint32_t(a.Hkv) * D * sizeof(T);
   const uint32_t nbytes = uint32_t(a.seq_len[bl]) * rowb;  // the sequence's new rows
+  const uint32_t obytes = uint32_t(a.seq_len[bl]) * uint32_t(a.Hq) * D * sizeof(T);  // the sequence's outputs
   const T* kn0 = sr.kin + (int64_t(sr.start) * a.Hkv + g) * D;  // this KV head's first new row
   const T* vn0 = sr.vin + (int64_t(sr.start) * a.Hkv + g) * D;
   const uint32_t hbytes = uint32_t(sr.p0 - sr.h0) * D * sizeof(T);  // the history rows
@@ -1496,13 +1528,10 @@ void prefill_main(PrefillArgs a) {
 
     // ---- 3. the next pass's loads, then this pass's outputs: value columns
     //         16ct+4lg .. +3 of query row hq
-    int64_t orow[QT];
-    bool ov[QT];
+    uint32_t orow[QT];  // byte offset of each output row among the sequence's (kOOB: no such row)
 #pragma unroll
-    for (int qt = 0; qt < QT; ++qt) {
-      orow[qt] = sr.qrow(c0 + ti[qt], hh[qt]) * D + 4 * lg;
-      ov[qt] = rv[qt];
-    }
+    for (int qt = 0; qt < QT; ++qt)
+      orow[qt] = rv[qt] ? uint32_t((c0 + ti[qt]) * sr.Hq + g * G + hh[qt]) * uint32_t(D * sizeof(T)) : kOOB;
     const bool more = !(last_pass && c0 + C >= s_hi);
     if (more) {
       if (last_pass) {
@@ -1523,14 +1552,14 @@ void prefill_main(PrefillArgs a) {
     for (int qt = 0; qt < QT; ++qt) {
       const float ls = lg_sum(l_run[qt]);
       const float inv = ls > 0.f ? 1.f / ls : 0.f;
-      if (ov[qt]) {
-        if constexpr (accum) {
+      if constexpr (accum) {
+        if (orow[qt] != kOOB) {
+          T* o = O + int64_t(sr.start) * sr.Hq * D + orow[qt] / sizeof(T) + 4 * lg;
 #pragma unroll
-          for (int ct = 0; ct < CT; ++ct) add4(O + orow[qt] + 16 * ct, acc[qt][ct], inv);
-        } else {
-#pragma unroll
-          for (int ct = 0; ct < CT; ++ct) store4(O + orow[qt] + 16 * ct, acc[qt][ct], inv);
+          for (int ct = 0; ct < CT; ++ct) add4(o + 16 * ct, acc[qt][ct], inv);
         }
+      } else {
+        store_row<CT>(make_rsrc(O + int64_t(sr.start) * sr.Hq * D, obytes), orow[qt], acc[qt], inv, T());
       }
     }
     if (!more) break;
