@@ -213,3 +213,12 @@ def test_max_window():
     out = case.decode_steps(st, q, k, v, 130, 140)
     case.check_decode(out, q, k, v, [130], 10, "W=2^20 decode")
     case.check_state(st, k, v, [140], "W=2^20")
+
+
+@pytest.mark.parametrize("phi", [0, 1, 2])
+@pytest.mark.parametrize("G,chunk", [(1, 64), (4, 64), (8, 64), (4, 256)])
+def test_no_band(phi, G, chunk):
+    """Calls over fully linear layers only (W = 0), whose passes load a pass
+    ahead: several passes per chunk, several slabs per chunk, ragged ends."""
+    case = Case([0, 0], batch=3, Hq=2 * G, Hkv=2, d=128, Df=128, dtype=torch.bfloat16, seed=23, phi=phi)
+    _prefill_from_empty(case, [321, 1, 64], chunk=chunk, label=f"no band phi={phi} G={G} chunk={chunk}")
