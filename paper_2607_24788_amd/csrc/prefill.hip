@@ -176,15 +176,23 @@ __device__ __forceinline__ void store8(float* dst, const Frag<float>& f) {
 template <int N> constexpr int row_a() { return N + 8; }
 template <int N> constexpr int row_t() { return N + 16; }
 
+// Where row r of Wf stands in its LDS copy: within each 32 rows, the first
+// halves of the four 8-row groups first, then their second halves.  A
+// fragment (rows 8g .. 8g+7 of a column in lane group g) then reads rows
+// 4g .. 4g+3 and 16+4g .. 16+4g+3 of the copy, whose banks differ between the
+// lane groups; in the natural order groups g and g + 1 read the same banks
+// (8 rows of 288 bytes are a multiple of the 64 banks).
+__device__ __forceinline__ int wf_row(int r) { return (r & ~31) | ((r & 4) << 2) | ((r & 24) >> 1) | (r & 3); }
+
 // Columns of Wf [D][DF] as MFMA fragments (rows d = 32kk + 8g .. +7 of column
-// col0 + lane%16): from a natural LDS copy, or (fp32, where the copy would not
-// fit next to the rest) from global memory.
+// col0 + lane%16): from an LDS copy (rows in wf_row order), or (fp32, where
+// the copy would not fit next to the rest) from global memory.
 template <typename T, int D, int DF, bool kLds>
 struct WfCols {
   const T* src;  // kLds: LDS [D][row_t<DF>]; else global [D][DF]
   __device__ __forceinline__ void col(Frag<T>& f, int kk, int col0) const {
     const int lane = threadIdx.x & 63, hq = lane & 15, lg = lane >> 4;
-    if constexpr (kLds) load_colfrag(f, src, row_t<DF>(), 32 * kk + 8 * lg, col0);
+    if constexpr (kLds) load_colfrag2(f, src, row_t<DF>(), 32 * kk + 4 * lg, 32 * kk + 16 + 4 * lg, col0);
     else f.load_strided(src + (32 * kk + 8 * lg) * DF + col0 + hq, DF);
   }
 };
@@ -243,7 +251,7 @@ __device__ __forceinline__ f32x4_t act4(f32x4_t x, int phi) {
   return f32x4_t{feat_act(x[0], phi), feat_act(x[1], phi), feat_act(x[2], phi), feat_act(x[3], phi)};
 }
 
-// Wf [D][DF] into LDS, natural layout (NTH threads cooperating; every load
+// Wf [D][DF] into LDS, rows in wf_row order (NTH threads cooperating; every load
 // is issued before the first store).
 template <typename T, int D, int DF, int NTH>
 __device__ __forceinline__ void stage_wf(const T* Wf, T* Wn) {
@@ -258,7 +266,7 @@ __device__ __forceinline__ void stage_wf(const T* Wf, T* Wn) {
 #pragma unroll
   for (int u = 0; u < N; ++u) {
     const int i = threadIdx.x + u * NTH, r = i / (DF / 8), ch = i - r * (DF / 8);
-    store8(Wn + r * WROW + 8 * ch, f[u]);
+    store8(Wn + wf_row(r) * WROW + 8 * ch, f[u]);
   }
 }
 
@@ -595,8 +603,9 @@ __global__ __launch_bounds__(kSegThreads) void prefill_segsum(PrefillArgs a) {
 #pragma unroll
       for (int kh = 0; kh < kSegSlab / 32; ++kh) {
         Frag<T> fv, fp;
-        load_colfrag(fv, vr, VROW, 32 * kh + 8 * lg, 16 * ct);
-        load_colfrag(fp, pr, PROW, 32 * kh + 8 * lg, 16 * ft);
+        // (keys 4lg .. +3 and 16 + 4lg .. +3: distinct LDS banks)
+        load_colfrag2(fv, vr, VROW, 32 * kh + 4 * lg, 32 * kh + 16 + 4 * lg, 16 * ct);
+        load_colfrag2(fp, pr, PROW, 32 * kh + 4 * lg, 32 * kh + 16 + 4 * lg, 16 * ft);
         sacc[x] = mma(fv, fp, sacc[x]);  // rows c = 16ct+4lg+i, column f = 16ft+hq
         if (ct == 0) zp += fp.sum();
       }
@@ -983,16 +992,27 @@ void prefill_main(PrefillArgs a) {
     const float* S0 = L.seg + (int64_t(a.seg0 + sg) * a.Hkv + g) * (int64_t(DF) * D + DF);
     constexpr int NS = DF * D / 4 / NTH;
     static_assert(NS * NTH * 4 == DF * D, "even split");
+    // a wave takes 16 rows x 4 column quads at a time: its transposed 4-byte
+    // stores then fall on 64 distinct banks (32 consecutive quads of two rows
+    // fell on 8)
+    static_assert(NTH % 64 == 0 && DF % 16 == 0 && D % 16 == 0, "16 x 4 blocks");
+    auto s_at = [&](int u, int& f, int& c4) {
+      const int blk = (tid + u * NTH) >> 6;
+      f = 16 * (blk / (D / 16)) + hq;
+      c4 = 16 * (blk % (D / 16)) + 4 * lg;
+    };
     float4 x[NS];
 #pragma unroll
     for (int u = 0; u < NS; ++u) {
-      const int i = tid + u * NTH, f = i / (D / 4), c4 = 4 * (i - f * (D / 4));
+      int f, c4;
+      s_at(u, f, c4);
       x[u] = *reinterpret_cast<const float4*>(S0 + f * D + c4);
     }
     const float zv = tid < DF ? S0[DF * D + tid] : 0.f;
 #pragma unroll
     for (int u = 0; u < NS; ++u) {
-      const int i = tid + u * NTH, f = i / (D / 4), c4 = 4 * (i - f * (D / 4));
+      int f, c4;
+      s_at(u, f, c4);
       St[(c4 + 0) * SROW + f] = x[u].x;
       St[(c4 + 1) * SROW + f] = x[u].y;
       St[(c4 + 2) * SROW + f] = x[u].z;
