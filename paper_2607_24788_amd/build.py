@@ -1,5 +1,5 @@
 """Compile the HIP sources under csrc/ into the in-tree shared library
-``libglide.so`` for gfx950 (hipcc, one object per source, built in parallel)."""
+``libglide.so`` for gfx950 (hipcc, one object per source or part of one, built in parallel)."""
 import concurrent.futures as cf
 import glob
 import os
@@ -23,22 +23,35 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17",
 # (masked scores are -inf, 0/0 is tested explicitly), so their max
 # reductions need no NaN quieting of matrix-core results.
 EXTRA = {"prefill.hip": ["-fno-honor-nans"]}
+# Sources compiled in several parts (one object each, built in parallel):
+# the prefill kernels once per element type and head dim.
+PARTS = {"prefill.hip": ("GLIDE_PREFILL_PART", 4)}
 
 
-def _compile(src):
-    obj = os.path.join(BUILD_DIR, os.path.basename(src) + ".o")
-    extra = EXTRA.get(os.path.basename(src), [])
+def _compile(job):
+    src, part = job
+    name = os.path.basename(src)
+    extra, obj = list(EXTRA.get(name, [])), os.path.join(BUILD_DIR, name + ".o")
+    if part is not None:
+        extra.append(f"-D{PARTS[name][0]}={part}")
+        obj = os.path.join(BUILD_DIR, f"{name}.{part}.o")
     r = subprocess.run([HIPCC, *FLAGS, *extra, "-c", src, "-o", obj], capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"hipcc failed on {src}:\n{r.stdout}\n{r.stderr}")
     return obj
 
 
+def _jobs(src):
+    name = os.path.basename(src)
+    return [(src, p) for p in range(PARTS[name][1])] if name in PARTS else [(src, None)]
+
+
 def build(verbose=False):
     os.makedirs(BUILD_DIR, exist_ok=True)
     srcs = sorted(glob.glob(os.path.join(CSRC, "*.hip")))
-    with cf.ThreadPoolExecutor(max_workers=min(8, len(srcs))) as ex:
-        objs = list(ex.map(_compile, srcs))
+    jobs = [j for s in srcs for j in _jobs(s)]
+    with cf.ThreadPoolExecutor(max_workers=min(8, len(jobs))) as ex:
+        objs = list(ex.map(_compile, jobs))
     tmp = LIB + ".tmp"
     r = subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs],
                        capture_output=True, text=True)

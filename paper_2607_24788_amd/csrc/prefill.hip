@@ -44,7 +44,6 @@ namespace {
 
 constexpr int kThreads = 256;  // helper kernels
 constexpr int kWaves = 4;
-constexpr int kRB = 256;       // main kernel: query rows per pass of a chunk
 constexpr float kLog2e = 1.4426950408889634f;
 
 // Rows of one (sequence, KV head) of a layer: new tokens come from the
@@ -685,20 +684,21 @@ __global__ __launch_bounds__(kThreads) void prefill_scan(PrefillArgs a) {
 // and the final normalisation are lane-local and the output leaves in 8-byte
 // (bf16) stores.
 //
-// The walk is software-pipelined over passes (256 query rows of a chunk):
+// The walk is software-pipelined over passes (RB query rows of a chunk):
 // the next pass's query rows, first slab of delayed keys and first band tile
 // are loaded before this pass's output stores.  Loads and stores retire in
 // order, so a load issued after the stores could only be waited for together
 // with them.
 //
-// A pass's 256 rows are spread over MW waves, 256 / MW rows (16-row q-tiles)
-// each: every K and V fragment read from a band tile feeds 256 / (16 MW)
-// q-tiles' MFMAs.  The workgroup's LDS (about 155 KB) admits one workgroup
-// per CU, so MW waves run MW / 4 per SIMD with 512 / (MW / 4) registers
-// each.
-template <typename T, int D>
-constexpr int main_waves() { return 8; }
-
+// A pass's RB rows are spread over MW waves, RB / MW rows (16-row q-tiles)
+// each: every K and V fragment read from a band tile feeds RB / (16 MW)
+// q-tiles' MFMAs.  At D = 128 the workgroup's LDS (about 155 KB) admits one
+// workgroup per CU.  RB is 256 on 8 waves (two q-tiles each) where a chunk has
+// that many rows (C tokens x G heads); a chunk of at most 128 or 64 rows takes
+// 128 rows on 8 waves or 64 on 4 (one q-tile each): every wave carries its
+// q-tiles' matrix work whether their rows exist or not, so the larger pass
+// multiplies mostly padding (C = 64, G = 1: three quarters of it; 512 tokens
+// x 4 heads, d = 64, fp32: 104 us per call in 256-row passes, 60 us in 64-row ones).
 template <typename T, int D, int DF>
 struct MainLds {
   static constexpr int NBUF = 2;  // band stages
@@ -734,12 +734,12 @@ struct MainLds {
 // (every factor <= 1, whatever the gates), and on the chunk's last pass
 // S_{c+1} = e^{G_e - G_{t0-1}} S_c + sum_j e^{G_e - G_j} phi(k_j)^T v_j,
 // G_e the chunk's last token, after the masked block has read phi(k).
-template <typename T, int D, int DF, int PHI, int PASS, bool GATED, int MW>
-__global__ __launch_bounds__(64 * MW) __attribute__((amdgpu_waves_per_eu(MW / 4, MW / 4)))
+template <typename T, int D, int DF, int PHI, int PASS, bool GATED, int RB, int MW>
+__global__ __launch_bounds__(64 * MW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void prefill_main(PrefillArgs a) {
   using LD = MainLds<T, D, DF>;
-  constexpr int NTH = 64 * MW, QT = kRB / (16 * MW);  // threads; 16-row q-tiles per wave
-  static_assert(QT * 16 * MW == kRB, "a pass's rows must spread evenly over the waves");
+  constexpr int NTH = 64 * MW, QT = RB / (16 * MW);  // threads; 16-row q-tiles per wave
+  static_assert(QT * 16 * MW == RB, "a pass's rows must spread evenly over the waves");
   constexpr int KS = D / 32, KSF = DF / 32, CT = D / 16, FT = DF / 16;
   constexpr int NT = FT * CT / MW;            // S tiles per wave (state update)
   constexpr int SL = LD::SLAB;
@@ -804,7 +804,7 @@ void prefill_main(PrefillArgs a) {
   };
 
   // ---- pass geometry: chunk c0 (nk tokens from absolute position t0), rows
-  //      [rb, rb + kRB) of its nrow = nk * G query rows
+  //      [rb, rb + RB) of its nrow = nk * G query rows
   int c0 = s_lo, rb = 0, nk = 0, nrow = 0, ti_min = 0, ti_max = 0, wti_max = 0, ntile = 0;
   bool last_pass = true;
   int64_t t0 = 0, klo = 0, khi = 0, kb0 = 0;
@@ -814,8 +814,8 @@ void prefill_main(PrefillArgs a) {
     nk = min(s_hi, c0 + C) - c0;
     t0 = sr.p0 + c0;
     nrow = nk * G;
-    last_pass = rb + kRB >= nrow;
-    const int r_end = min(nrow, rb + kRB);
+    last_pass = rb + RB >= nrow;
+    const int r_end = min(nrow, rb + RB);
     ti_min = rb / G;
     ti_max = (r_end - 1) / G;
     wti_max = min(r_end - 1, rb + 16 * QT * (wave + 1) - 1) / G;
@@ -1454,7 +1454,7 @@ void prefill_main(PrefillArgs a) {
             refresh();
             // (after the walk's last pass: that pass again, never waited for)
             const int cn = last_pass && c0 + C < s_hi ? c0 + C : c0;
-            const int rn = last_pass ? (cn == c0 ? rb : 0) : rb + kRB;
+            const int rn = last_pass ? (cn == c0 ? rb : 0) : rb + RB;
             load_q_of(cn, rn);
             load_slab(sr.p0 + cn, min(s_hi, cn + C) - cn, 0);
           }
@@ -1588,7 +1588,7 @@ void prefill_main(PrefillArgs a) {
         c0 += C;
         rb = 0;
       } else {
-        rb += kRB;
+        rb += RB;
       }
       geom();
     }
@@ -1706,36 +1706,46 @@ __global__ void prefill_advance(PrefillArgs a) {
   }
 }
 
+// The main kernel over the launch's (segment, KV head, layer) grid, with RB
+// query rows per pass on MW waves.
+template <typename T, int D, int DF, int RB, int MW>
+void main_t(const PrefillArgs& a, int pass, hipStream_t s) {
+  const dim3 grid(a.nseg, a.Hkv, unsigned(a.nlayer)), block(64 * MW);
+  if (a.gated) {  // the shared denominator only
+    if (a.phi == GLIDE_PHI_SOFTMAX) hipLaunchKernelGGL((prefill_main<T, D, DF, 2, 0, true, RB, MW>), grid, block, 0, s, a);
+    else if (a.phi) hipLaunchKernelGGL((prefill_main<T, D, DF, 1, 0, true, RB, MW>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((prefill_main<T, D, DF, 0, 0, true, RB, MW>), grid, block, 0, s, a);
+    return;
+  }
+  if (a.phi == GLIDE_PHI_SOFTMAX) {
+    if (pass == 0) hipLaunchKernelGGL((prefill_main<T, D, DF, 2, 0, false, RB, MW>), grid, block, 0, s, a);
+    if (pass == 1) hipLaunchKernelGGL((prefill_main<T, D, DF, 2, 1, false, RB, MW>), grid, block, 0, s, a);
+    if (pass == 2) hipLaunchKernelGGL((prefill_main<T, D, DF, 2, 2, false, RB, MW>), grid, block, 0, s, a);
+  } else if (a.phi) {
+    if (pass == 0) hipLaunchKernelGGL((prefill_main<T, D, DF, 1, 0, false, RB, MW>), grid, block, 0, s, a);
+    if (pass == 1) hipLaunchKernelGGL((prefill_main<T, D, DF, 1, 1, false, RB, MW>), grid, block, 0, s, a);
+    if (pass == 2) hipLaunchKernelGGL((prefill_main<T, D, DF, 1, 2, false, RB, MW>), grid, block, 0, s, a);
+  } else {
+    if (pass == 0) hipLaunchKernelGGL((prefill_main<T, D, DF, 0, 0, false, RB, MW>), grid, block, 0, s, a);
+    if (pass == 1) hipLaunchKernelGGL((prefill_main<T, D, DF, 0, 1, false, RB, MW>), grid, block, 0, s, a);
+    if (pass == 2) hipLaunchKernelGGL((prefill_main<T, D, DF, 0, 2, false, RB, MW>), grid, block, 0, s, a);
+  }
+}
+
 // The kernels of one prefill launch, for the a.nlayer layers of a.layers
 // (the grid's last dimension runs over them, longest windows first).
 template <typename T, int D, int DF>
 hipError_t layer_t(const PrefillArgs& a, hipStream_t s) {
-  constexpr int MW = main_waves<T, D>();
   hipError_t e;
   const unsigned nl = unsigned(a.nlayer);
   bool window = false;
   for (int i = 0; i < a.nlayer; ++i) window = window || a.layers[i].W > 0;
+  // rows per pass: the smallest that holds a whole chunk's C * G rows
+  const int rows = a.C * a.G;
   auto main = [&](int pass) {
-    const dim3 grid(a.nseg, a.Hkv, nl), block(64 * MW);
-    if (a.gated) {  // the shared denominator only
-      if (a.phi == GLIDE_PHI_SOFTMAX) hipLaunchKernelGGL((prefill_main<T, D, DF, 2, 0, true, MW>), grid, block, 0, s, a);
-      else if (a.phi) hipLaunchKernelGGL((prefill_main<T, D, DF, 1, 0, true, MW>), grid, block, 0, s, a);
-      else hipLaunchKernelGGL((prefill_main<T, D, DF, 0, 0, true, MW>), grid, block, 0, s, a);
-      return;
-    }
-    if (a.phi == GLIDE_PHI_SOFTMAX) {
-      if (pass == 0) hipLaunchKernelGGL((prefill_main<T, D, DF, 2, 0, false, MW>), grid, block, 0, s, a);
-      if (pass == 1) hipLaunchKernelGGL((prefill_main<T, D, DF, 2, 1, false, MW>), grid, block, 0, s, a);
-      if (pass == 2) hipLaunchKernelGGL((prefill_main<T, D, DF, 2, 2, false, MW>), grid, block, 0, s, a);
-    } else if (a.phi) {
-      if (pass == 0) hipLaunchKernelGGL((prefill_main<T, D, DF, 1, 0, false, MW>), grid, block, 0, s, a);
-      if (pass == 1) hipLaunchKernelGGL((prefill_main<T, D, DF, 1, 1, false, MW>), grid, block, 0, s, a);
-      if (pass == 2) hipLaunchKernelGGL((prefill_main<T, D, DF, 1, 2, false, MW>), grid, block, 0, s, a);
-    } else {
-      if (pass == 0) hipLaunchKernelGGL((prefill_main<T, D, DF, 0, 0, false, MW>), grid, block, 0, s, a);
-      if (pass == 1) hipLaunchKernelGGL((prefill_main<T, D, DF, 0, 1, false, MW>), grid, block, 0, s, a);
-      if (pass == 2) hipLaunchKernelGGL((prefill_main<T, D, DF, 0, 2, false, MW>), grid, block, 0, s, a);
-    }
+    if (rows <= 64) main_t<T, D, DF, 64, 4>(a, pass, s);
+    else if (rows <= 128) main_t<T, D, DF, 128, 8>(a, pass, s);
+    else main_t<T, D, DF, 256, 8>(a, pass, s);
   };
   if (a.gated) {  // the new tokens' cumulative log-gates, before any kernel reads them
     hipLaunchKernelGGL((prefill_gates<T, D, DF>), dim3(a.nseq, a.Hkv, nl), dim3(kThreads), 0, s, a);
@@ -1790,27 +1800,49 @@ hipError_t gather_t(const PrefillArgs& a, hipStream_t s) {
 
 }  // namespace
 
-#define GLIDE_DISPATCH(FN, ...)                                                   \
-  do {                                                                            \
-    if (dtype == GLIDE_BF16) {                                                    \
-      if (d == 128 && Df == 128) return FN<bf16_t, 128, 128>(__VA_ARGS__);        \
-      if (d == 128 && Df == 64) return FN<bf16_t, 128, 64>(__VA_ARGS__);          \
-      if (d == 64 && Df == 128) return FN<bf16_t, 64, 128>(__VA_ARGS__);         \
-      if (d == 64 && Df == 64) return FN<bf16_t, 64, 64>(__VA_ARGS__);           \
-    } else {                                                                      \
-      if (d == 128 && Df == 128) return FN<float, 128, 128>(__VA_ARGS__);         \
-      if (d == 128 && Df == 64) return FN<float, 128, 64>(__VA_ARGS__);           \
-      if (d == 64 && Df == 128) return FN<float, 64, 128>(__VA_ARGS__);          \
-      if (d == 64 && Df == 64) return FN<float, 64, 64>(__VA_ARGS__);            \
-    }                                                                             \
-    return hipErrorInvalidValue;                                                  \
-  } while (0)
+// Compiled once per element type and head dim (GLIDE_PREFILL_PART, see
+// build.py), so that the parts build in parallel; part 0 holds the dispatch.
+#ifndef GLIDE_PREFILL_PART
+#error "compile with GLIDE_PREFILL_PART = 0 .. 3"
+#endif
+#if GLIDE_PREFILL_PART < 2
+using part_t = bf16_t;
+#else
+using part_t = float;
+#endif
+constexpr int kPartD = GLIDE_PREFILL_PART % 2 == 0 ? 128 : 64;
+#define GLIDE_PART_NAME2(n, p) n##p
+#define GLIDE_PART_NAME(n, p) GLIDE_PART_NAME2(n, p)
+
+hipError_t GLIDE_PART_NAME(prefill_layer_part, GLIDE_PREFILL_PART)(const PrefillArgs& a, int Df, hipStream_t s) {
+  if (Df == 128) return layer_t<part_t, kPartD, 128>(a, s);
+  if (Df == 64) return layer_t<part_t, kPartD, 64>(a, s);
+  return hipErrorInvalidValue;
+}
+hipError_t GLIDE_PART_NAME(prefill_gather_part, GLIDE_PREFILL_PART)(const PrefillArgs& a, int Df, hipStream_t s) {
+  if (Df == 128) return gather_t<part_t, kPartD, 128>(a, s);
+  if (Df == 64) return gather_t<part_t, kPartD, 64>(a, s);
+  return hipErrorInvalidValue;
+}
+
+#if GLIDE_PREFILL_PART == 0
+hipError_t prefill_layer_part1(const PrefillArgs&, int, hipStream_t);
+hipError_t prefill_layer_part2(const PrefillArgs&, int, hipStream_t);
+hipError_t prefill_layer_part3(const PrefillArgs&, int, hipStream_t);
+hipError_t prefill_gather_part1(const PrefillArgs&, int, hipStream_t);
+hipError_t prefill_gather_part2(const PrefillArgs&, int, hipStream_t);
+hipError_t prefill_gather_part3(const PrefillArgs&, int, hipStream_t);
 
 hipError_t launch_prefill_layer(const PrefillArgs& a, int d, int Df, int dtype, hipStream_t s) {
-  GLIDE_DISPATCH(layer_t, a, s);
+  if (d != 64 && d != 128) return hipErrorInvalidValue;
+  if (dtype == GLIDE_BF16) return d == 128 ? prefill_layer_part0(a, Df, s) : prefill_layer_part1(a, Df, s);
+  return d == 128 ? prefill_layer_part2(a, Df, s) : prefill_layer_part3(a, Df, s);
 }
 hipError_t launch_prefill_gather(const PrefillArgs& a, int d, int Df, int dtype, hipStream_t s) {
-  GLIDE_DISPATCH(gather_t, a, s);
+  if (d != 64 && d != 128) return hipErrorInvalidValue;
+  if (dtype == GLIDE_BF16) return d == 128 ? prefill_gather_part0(a, Df, s) : prefill_gather_part1(a, Df, s);
+  return d == 128 ? prefill_gather_part2(a, Df, s) : prefill_gather_part3(a, Df, s);
 }
+#endif
 
 }  // namespace glide

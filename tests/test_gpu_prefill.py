@@ -222,3 +222,12 @@ def test_no_band(phi, G, chunk):
     ahead: several passes per chunk, several slabs per chunk, ragged ends."""
     case = Case([0, 0], batch=3, Hq=2 * G, Hkv=2, d=128, Df=128, dtype=torch.bfloat16, seed=23, phi=phi)
     _prefill_from_empty(case, [321, 1, 64], chunk=chunk, label=f"no band phi={phi} G={G} chunk={chunk}")
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("G,chunk", [(1, 32), (1, 64), (2, 64), (1, 96), (4, 32), (3, 64), (1, 160)])
+def test_rows_per_pass(dtype, G, chunk):
+    """Chunks of C * G rows around the 64- and 128-row passes (full, partly
+    filled, and one row past), with and without a band."""
+    case = Case([0, 5, 70], batch=2, Hq=2 * G, Hkv=2, d=128, Df=64, dtype=dtype, seed=22)
+    _prefill_from_empty(case, [161, 95], chunk=chunk, label=f"G={G} chunk={chunk}")
