@@ -703,21 +703,32 @@ struct PrefillArgs {
 static_assert(sizeof(PrefillArgs) <= 4096, "kernel argument block");
 
 // Segments hold at least kMinSegTokens tokens, which bounds the records.
-constexpr int kMinSegTokens = 128;
+constexpr int kMinSegTokens = 64;
 
-// Chunks per prefill segment, for a launch of nl layers: at least
-// kMinSegTokens tokens, and about kSegRounds workgroups per CU over the
-// launch's (segment, KV head, layer) grid when the call is large enough
-// (longer segments amortise each workgroup's start, the state load, over
-// more chunks; several rounds keep the CUs evenly loaded across layers of
-// different windows); at most 16 chunks walked in order by one workgroup.
-// More layers per launch never give shorter segments, so the workspace's
-// record bound, taken at nl = 1, holds for every launch.
+// Chunks per prefill segment, for a launch of nl layers: about kSegRounds
+// workgroups per CU over the launch's (segment, KV head, layer) grid when the
+// call is large enough (longer segments amortise each workgroup's start, the
+// state load, over more chunks; several rounds keep the CUs evenly loaded
+// across layers of different windows), at most 16 chunks walked in order by
+// one workgroup.  A smaller call takes the shorter time by a simple model of
+// the main kernel: rounds of one workgroup per CU, each its chunks plus a
+// start worth 0.4 of a chunk, over segments of about 128 tokens or half
+// as many (never under kMinSegTokens).  512 tokens x 4 heads (fp32, W = 64):
+// one round of one chunk in place of two, 60 -> 41.7 us per call; 8 x 301 ..
+// 2047 tokens x 8 heads (W = 1000): five rounds of one in place of three of
+// two, 430 -> 413 us.
 constexpr int kSegRounds = 8;
+constexpr int kSegCus = 256;
 inline int32_t segment_chunks(int64_t T, int Hkv, int32_t chunk, int32_t nl) {
-  const int32_t lo = (kMinSegTokens + chunk - 1) / chunk;
-  const int64_t fill = T * Hkv * nl / (int64_t(chunk) * 256 * kSegRounds);
-  return int32_t(fill > lo ? (fill < 16 ? fill : 16) : lo);
+  const int64_t fill = T * Hkv * nl / (int64_t(chunk) * kSegCus * kSegRounds);
+  const int32_t lo = (2 * kMinSegTokens + chunk - 1) / chunk;
+  if (fill > lo) return int32_t(fill < 16 ? fill : 16);
+  const int32_t half = (kMinSegTokens + chunk - 1) / chunk;
+  auto cost = [&](int32_t n) {  // in tenths of a chunk's time
+    const int64_t wgs = (T + int64_t(n) * chunk - 1) / (int64_t(n) * chunk) * Hkv * nl;
+    return (wgs + kSegCus - 1) / kSegCus * (10 * n + 4);
+  };
+  return half < lo && cost(half) < cost(lo) ? half : lo;
 }
 
 struct PrefillWorkspace {
