@@ -442,11 +442,6 @@ glide_status glide_prefill(const glide_config* cfg, void* state, size_t state_by
   if (!aligned(workspace, 256)) return GLIDE_ERR_ALIGN;
   if (total_tokens == 0) return GLIDE_OK;
 
-  // Tokens still pending from decode steps are folded first, so the state
-  // the chunked pass starts from is S = sum_{j < max(0, p - W)}.
-  s = glide_state_flush(cfg, state, state_bytes, layer0, n_layers, phi_w, stream);
-  if (s != GLIDE_OK) return s;
-
   const int64_t T = total_tokens;
   const int B = cfg->batch, Hq = cfg->n_q_heads, Hkv = cfg->n_kv_heads, d = cfg->head_dim, Df = cfg->feat_dim;
   const int es = esize(cfg);
@@ -539,8 +534,10 @@ glide_status glide_prefill(const glide_config* cfg, void* state, size_t state_by
     for (int g0 = 0; g0 < B; g0 += kMaxSeqPerLaunch) {
       const int32_t nseg = group(g0, seg0);
       if (window) {
-        // history of a continuing prefill (nothing to copy when pos == 0)
-        s = hip_status(launch_prefill_gather(a, d, Df, cfg->dtype, st));
+        // tokens still pending from decode steps folded, so that the chunked
+        // pass starts from S = sum_{j < max(0, p - W)}, and the history of a
+        // continuing prefill (nothing to do when pos == 0)
+        s = hip_status(launch_prefill_begin(a, d, Df, cfg->dtype, st));
         if (s != GLIDE_OK) return s;
       }
       s = hip_status(launch_prefill_layer(a, d, Df, cfg->dtype, st));

@@ -773,7 +773,6 @@ inline int32_t prefill_layers_per_launch(int32_t n_layers, size_t bytes, SlotFn 
 }
 
 hipError_t launch_prefill_layer(const PrefillArgs& a, int d, int Df, int dtype, hipStream_t stream);
-hipError_t launch_prefill_gather(const PrefillArgs& a, int d, int Df, int dtype, hipStream_t stream);
-hipError_t launch_prefill_ringfill(const PrefillArgs& a, int d, int Df, int dtype, hipStream_t stream);
+hipError_t launch_prefill_begin(const PrefillArgs& a, int d, int Df, int dtype, hipStream_t stream);
 
 }  // namespace glide

@@ -9,8 +9,10 @@
 // block), and S_{c+1} = S_c + the sum over the chunk's C delayed keys.
 //
 // Kernels (per layer):
-//   gather   ring tokens [max(0,p0-W), p0) of a continuing prefill into a
-//            natural-layout side buffer (the "history");
+//   begin    ring tokens [max(0,p0-W), p0) of a continuing prefill into a
+//            natural-layout side buffer (the "history"), and, beside it, the
+//            tokens decode steps left pending folded (flush_unit): the
+//            incoming state is then S = sum_{j < p0-W};
 //   segsum   per (sequence, KV head, segment of chunks): the segment's state
 //            increment from its delayed keys (MFMA, keys as the reduction);
 //   scan     exclusive prefix over segments on top of the incoming state;
@@ -24,9 +26,10 @@
 //            feeds S_{c+1}), all scaled by 2^-m so that they add straight
 //            onto the band's numerator and denominator (the shared-denominator
 //            merge, in the band's frame);
-//   ringfill the last W tokens into the ring;   advance: pos += T_b.
-// Tokens a decode step left pending are folded (glide_state_flush) before the
-// first of these kernels runs, so the incoming state is S = sum_{j < p0-W}.
+//   end      the last W tokens into the ring, then pos += T_b.
+// A launch costs 4 to 5 us on the stream whatever it does, so the kernels
+// around the three that compute are two, not four (512 tokens x 4 heads,
+// fp32: 41.7 -> 38.7 us per call).
 //
 // The feature map phi(x) = max(0, x Wf) is evaluated where it is needed, on
 // MFMA against Wf.  phi(q) is produced transposed (features as MFMA rows),
@@ -36,6 +39,7 @@
 // and the delayed keys' phi(k)).
 #include <math.h>
 
+#include "flush.h"
 #include "glide_internal.h"
 
 namespace glide {
@@ -384,12 +388,23 @@ __device__ __forceinline__ void phi_slab(const WfCols<T, D, DF, kLds>& wf, const
 }
 
 // ---------------------------------------------------------------------------
-// gather: history tokens [h0, p0) of a continuing prefill, ring -> [b][g][Wcap][d]
+// begin: workgroup 0 of each (sequence, KV head) folds its pending tokens (it
+// writes S, z and nf, which no other workgroup here reads); the others gather
+// the history tokens [h0, p0) of a continuing prefill, ring ->
+// [b][g][Wcap][d].
 template <typename T, int D, int DF>
-__global__ __launch_bounds__(kThreads) void prefill_gather(PrefillArgs a) {
+__global__ __launch_bounds__(kThreads) void prefill_begin(PrefillArgs a) {
   const int bl = blockIdx.y, g = int(blockIdx.z) % a.Hkv;
   const LayerView L = layer_view(a, int(blockIdx.z) / a.Hkv);
   if (L.W == 0) return;
+  if (blockIdx.x == 0) {
+    if (a.linear && L.Wd > 0)
+      flush_unit<T, D, DF, kThreads>(L.base, a.B, a.Hkv, L.W, L.R, int64_t(a.seq0 + bl) * a.Hkv + g,
+                                     reinterpret_cast<const T*>(static_cast<const char*>(L.wf) + int64_t(g) * a.wf_hs),
+                                     a.phi, a.gated != 0);
+    return;
+  }
+  const int part = blockIdx.x - 1, stride = (gridDim.x - 1) * kThreads;
   const SeqRows<T, D> sr = seq_rows<T, D, DF>(a, L, bl, g);
   const int n = int(sr.p0 - sr.h0);
   if (n <= 0) return;
@@ -400,9 +415,8 @@ __global__ __launch_bounds__(kThreads) void prefill_gather(PrefillArgs a) {
   T* hk = static_cast<T*>(L.hk) + unit * a.Wcap * D;
   T* hv = static_cast<T*>(L.hv) + unit * a.Wcap * D;
   constexpr int CPR = D / 8;
-  const int stride = gridDim.x * kThreads;
   // keys: a slot's row is made of 16-byte chunks (8 columns), moved whole
-  for (int idx = blockIdx.x * kThreads + threadIdx.x; idx < n * CPR; idx += stride) {
+  for (int idx = part * kThreads + threadIdx.x; idx < n * CPR; idx += stride) {
     const int i = idx / CPR, ch = idx - i * CPR;
     Frag<T> f;
     f.load(Kr + kring_elem(int32_t((sr.h0 + i) % L.R), 8 * ch, D));
@@ -414,7 +428,7 @@ __global__ __launch_bounds__(kThreads) void prefill_gather(PrefillArgs a) {
   // consecutive columns)
   const int64_t m0 = sr.h0 >> 3;
   const int ng = int(((sr.p0 - 1) >> 3) - m0 + 1);
-  for (int idx = blockIdx.x * kThreads + threadIdx.x; idx < ng * D; idx += stride) {
+  for (int idx = part * kThreads + threadIdx.x; idx < ng * D; idx += stride) {
     const int gi = idx / D, c = idx - gi * D;
     const int64_t j0 = (m0 + gi) * 8;
     T x[8];
@@ -427,7 +441,7 @@ __global__ __launch_bounds__(kThreads) void prefill_gather(PrefillArgs a) {
     const LayerSections sg = layer_sections(a.B, a.Hkv, D, DF, L.R, sizeof(T), true);
     const double* grg = reinterpret_cast<const double*>(L.base + sg.GR) + unit * L.R;
     double* hg = reinterpret_cast<double*>(a.ws + int64_t(L.ls) * a.ws_slot + a.ws_hg) + unit * a.Wcap;
-    for (int i = blockIdx.x * kThreads + threadIdx.x; i < n; i += gridDim.x * kThreads) hg[i] = grg[(sr.h0 + i) % L.R];
+    for (int i = part * kThreads + threadIdx.x; i < n; i += stride) hg[i] = grg[(sr.h0 + i) % L.R];
   }
 }
 
@@ -1628,12 +1642,15 @@ void prefill_main(PrefillArgs a) {
 // 8 consecutive tokens (R is a multiple of 8, so such a group never wraps)
 // and stores it at once, or element by element where the group is only partly
 // in range (its other slots may hold live tokens).
+// Then advance: pos += T_b; the scan left S, z = the sums over tokens
+// [0, max(0, pos - Wd)), nothing pending.  Every workgroup of a unit reads the
+// old pos, so the last of them to finish writes the new one: each waits for
+// its own reads, then adds one to the unit's count (zero between calls; the
+// last resets it).
 template <typename T, int D, int DF>
-__global__ __launch_bounds__(kThreads) void prefill_ringfill(PrefillArgs a) {
-  const int bl = blockIdx.y, g = int(blockIdx.z) % a.Hkv;
-  const LayerView L = layer_view(a, int(blockIdx.z) / a.Hkv);
+__device__ __forceinline__ void ring_fill(const PrefillArgs& a, const LayerView& L, const SeqRows<T, D>& sr, int bl,
+                                          int g) {
   if (L.W == 0) return;
-  const SeqRows<T, D> sr = seq_rows<T, D, DF>(a, L, bl, g);
   const int Tb = a.seq_len[bl];
   const int64_t pend = sr.p0 + Tb;
   int64_t jlo = pend - L.W;
@@ -1680,27 +1697,39 @@ __global__ __launch_bounds__(kThreads) void prefill_ringfill(PrefillArgs a) {
   }
 }
 
-// advance: pos += T_b (after every other kernel of the layer read pos); the
-// scan left S, z = the sums over tokens [0, max(0, pos - Wd)), nothing
-// pending.
 template <typename T, int D, int DF>
-__global__ void prefill_advance(PrefillArgs a) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= a.nseq * a.Hkv) return;
-  const LayerView L = layer_view(a, blockIdx.y);
-  const int bl = i / a.Hkv, g = i - bl * a.Hkv;
+__global__ __launch_bounds__(kThreads) void prefill_end(PrefillArgs a) {
+  __shared__ int last;
+  const int bl = blockIdx.y, g = int(blockIdx.z) % a.Hkv;
+  const LayerView L = layer_view(a, int(blockIdx.z) / a.Hkv);
+  const SeqRows<T, D> sr = seq_rows<T, D, DF>(a, L, bl, g);
+  ring_fill<T, D, DF>(a, L, sr, bl, g);
   const LayerSections sec = layer_sections(a.B, a.Hkv, D, DF, L.R, sizeof(T));
   const int64_t unit = int64_t(a.seq0 + bl) * a.Hkv + g;
-  int64_t* pos = reinterpret_cast<int64_t*>(L.base + sec.pos) + unit;
-  int64_t* nf = reinterpret_cast<int64_t*>(L.base + sec.nf) + unit;
-  const int64_t p = *pos + a.seq_len[bl];
-  *pos = p;
-  *nf = p - L.Wd > 0 ? p - L.Wd : 0;
-  if (a.gated && a.seq_len[bl] > 0) {  // G_{p-1}; the scan left S, z decayed to it
+  if (gridDim.x > 1) {
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      int* cnt = reinterpret_cast<int*>(L.base + sec.cnt) + unit;
+      last = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == int(gridDim.x) - 1;
+      if (last) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (!last) return;
+  } else {
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+  }
+  if (threadIdx.x != 0) return;
+  const int Tb = a.seq_len[bl];
+  const int64_t p = sr.p0 + Tb;
+  reinterpret_cast<int64_t*>(L.base + sec.pos)[unit] = p;
+  reinterpret_cast<int64_t*>(L.base + sec.nf)[unit] = p - L.Wd > 0 ? p - L.Wd : 0;
+  if (a.gated && Tb > 0) {  // G_{p-1}; the scan left S, z decayed to it
     const LayerSections sg = layer_sections(a.B, a.Hkv, D, DF, L.R, sizeof(T), true);
     double* gst = reinterpret_cast<double*>(L.base + sg.G) + 2 * unit;
     const double* gc = reinterpret_cast<const double*>(a.ws + int64_t(L.ls) * a.ws_slot + a.ws_gc);
-    const double ge = gc[(int64_t(a.seq_start[bl]) + a.seq_len[bl] - 1) * a.Hkv + g];
+    const double ge = gc[(int64_t(a.seq_start[bl]) + Tb - 1) * a.Hkv + g];
     gst[0] = ge;
     gst[1] = ge;
   }
@@ -1783,17 +1812,21 @@ hipError_t layer_t(const PrefillArgs& a, hipStream_t s) {
       }
     }
   }
-  if (window) {
-    hipLaunchKernelGGL((prefill_ringfill<T, D, DF>), dim3(32, a.nseq, a.Hkv * nl), dim3(kThreads), 0, s, a);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL((prefill_advance<T, D, DF>), dim3((a.nseq * a.Hkv + 255) / 256, nl), dim3(256), 0, s, a);
+  // workgroups per unit: about two 16-byte chunks per thread, at most 32
+  int64_t fill = 0;
+  for (int i = 0; i < a.nseq; ++i) fill = a.seq_len[i] > fill ? a.seq_len[i] : fill;
+  int64_t wmax = 0;
+  for (int i = 0; i < a.nlayer; ++i) wmax = a.layers[i].W > wmax ? a.layers[i].W : wmax;
+  if (fill > wmax) fill = wmax;
+  int64_t nx = (fill * (D / 8) + 2 * kThreads - 1) / (2 * kThreads);
+  nx = nx < 1 ? 1 : nx > 32 ? 32 : nx;
+  hipLaunchKernelGGL((prefill_end<T, D, DF>), dim3(unsigned(nx), a.nseq, a.Hkv * nl), dim3(kThreads), 0, s, a);
   return hipGetLastError();
 }
 
 template <typename T, int D, int DF>
-hipError_t gather_t(const PrefillArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL((prefill_gather<T, D, DF>), dim3(16, a.nseq, a.Hkv * unsigned(a.nlayer)), dim3(kThreads), 0,
+hipError_t begin_t(const PrefillArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL((prefill_begin<T, D, DF>), dim3(17, a.nseq, a.Hkv * unsigned(a.nlayer)), dim3(kThreads), 0,
                      s, a);
   return hipGetLastError();
 }
@@ -1819,9 +1852,9 @@ hipError_t GLIDE_PART_NAME(prefill_layer_part, GLIDE_PREFILL_PART)(const Prefill
   if (Df == 64) return layer_t<part_t, kPartD, 64>(a, s);
   return hipErrorInvalidValue;
 }
-hipError_t GLIDE_PART_NAME(prefill_gather_part, GLIDE_PREFILL_PART)(const PrefillArgs& a, int Df, hipStream_t s) {
-  if (Df == 128) return gather_t<part_t, kPartD, 128>(a, s);
-  if (Df == 64) return gather_t<part_t, kPartD, 64>(a, s);
+hipError_t GLIDE_PART_NAME(prefill_begin_part, GLIDE_PREFILL_PART)(const PrefillArgs& a, int Df, hipStream_t s) {
+  if (Df == 128) return begin_t<part_t, kPartD, 128>(a, s);
+  if (Df == 64) return begin_t<part_t, kPartD, 64>(a, s);
   return hipErrorInvalidValue;
 }
 
@@ -1829,19 +1862,19 @@ hipError_t GLIDE_PART_NAME(prefill_gather_part, GLIDE_PREFILL_PART)(const Prefil
 hipError_t prefill_layer_part1(const PrefillArgs&, int, hipStream_t);
 hipError_t prefill_layer_part2(const PrefillArgs&, int, hipStream_t);
 hipError_t prefill_layer_part3(const PrefillArgs&, int, hipStream_t);
-hipError_t prefill_gather_part1(const PrefillArgs&, int, hipStream_t);
-hipError_t prefill_gather_part2(const PrefillArgs&, int, hipStream_t);
-hipError_t prefill_gather_part3(const PrefillArgs&, int, hipStream_t);
+hipError_t prefill_begin_part1(const PrefillArgs&, int, hipStream_t);
+hipError_t prefill_begin_part2(const PrefillArgs&, int, hipStream_t);
+hipError_t prefill_begin_part3(const PrefillArgs&, int, hipStream_t);
 
 hipError_t launch_prefill_layer(const PrefillArgs& a, int d, int Df, int dtype, hipStream_t s) {
   if (d != 64 && d != 128) return hipErrorInvalidValue;
   if (dtype == GLIDE_BF16) return d == 128 ? prefill_layer_part0(a, Df, s) : prefill_layer_part1(a, Df, s);
   return d == 128 ? prefill_layer_part2(a, Df, s) : prefill_layer_part3(a, Df, s);
 }
-hipError_t launch_prefill_gather(const PrefillArgs& a, int d, int Df, int dtype, hipStream_t s) {
+hipError_t launch_prefill_begin(const PrefillArgs& a, int d, int Df, int dtype, hipStream_t s) {
   if (d != 64 && d != 128) return hipErrorInvalidValue;
-  if (dtype == GLIDE_BF16) return d == 128 ? prefill_gather_part0(a, Df, s) : prefill_gather_part1(a, Df, s);
-  return d == 128 ? prefill_gather_part2(a, Df, s) : prefill_gather_part3(a, Df, s);
+  if (dtype == GLIDE_BF16) return d == 128 ? prefill_begin_part0(a, Df, s) : prefill_begin_part1(a, Df, s);
+  return d == 128 ? prefill_begin_part2(a, Df, s) : prefill_begin_part3(a, Df, s);
 }
 #endif
 
