@@ -498,8 +498,15 @@ struct SegLds {
   static constexpr size_t bytes = (size_t(D) * WROW + size_t(kSegSlab) * (PROW + VROW)) * sizeof(T);
 };
 
+// bf16: 128 registers at most, so that two workgroups share a CU (their LDS is
+// 74 KB each at D = 128): one computes while the other waits at a barrier or
+// for its slab (this kernel: 198 -> 173 us over 4 x 32K tokens,
+// 308 -> 266 us over the batch-1 stack).  fp32:
+// the LDS admits one workgroup.
 template <typename T, int D, int DF, int PHI>
-__global__ __launch_bounds__(kSegThreads) void prefill_segsum(PrefillArgs a) {
+__global__ __launch_bounds__(kSegThreads)
+__attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 ? 4 : 2, sizeof(T) == 2 ? 4 : 2)))
+void prefill_segsum(PrefillArgs a) {
   using LD = SegLds<T, D, DF>;
   constexpr int CT = D / 16, FT = DF / 16, CPR = D / 8;
   constexpr int NT = FT * CT / kSegWaves;                  // dS tiles per wave
