@@ -715,8 +715,9 @@ __global__ __launch_bounds__(kThreads) void prefill_scan(PrefillArgs a) {
 // each: every K and V fragment read from a band tile feeds RB / (16 MW)
 // q-tiles' MFMAs.  At D = 128 the workgroup's LDS (about 155 KB) admits one
 // workgroup per CU.  RB is 256 on 8 waves (two q-tiles each) where a chunk has
-// that many rows (C tokens x G heads); a chunk of at most 128 or 64 rows takes
-// 128 rows on 8 waves or 64 on 4 (one q-tile each): every wave carries its
+// that many rows (C tokens x G heads); a chunk of at most 128 rows takes 128
+// on 8 waves, and one of at most 64 rows may take 64 on 4 (one q-tile each;
+// layer_t chooses): every wave carries its
 // q-tiles' matrix work whether their rows exist or not, so the larger pass
 // multiplies mostly padding (C = 64, G = 1: three quarters of it; 512 tokens
 // x 4 heads, d = 64, fp32: 104 us per call in 256-row passes, 60 us in 64-row ones).
@@ -1796,11 +1797,26 @@ hipError_t layer_t(const PrefillArgs& a, hipStream_t s) {
   const unsigned nl = unsigned(a.nlayer);
   bool window = false;
   for (int i = 0; i < a.nlayer; ++i) window = window || a.layers[i].W > 0;
-  // rows per pass: the smallest that holds a whole chunk's C * G rows
+  // Rows per pass, by a chunk's C * G rows.  64 rows on 4 waves multiply the
+  // least padding, but the pass's work that is not per row (phi of the delayed
+  // keys, the state update, staging) is then spread over 4 waves, not 8.  fp32
+  // pays most for padding (16 times the matrix cycles): always.  bf16: only
+  // where two workgroups share a CU (LDS) and there are enough of them; one per
+  // CU is better with 8 waves.  C = 64, G = 1, bf16, us per call, 64 rows
+  // against 128: d = 64, 4 x 16K tokens: W = 0 99 / 121, W = 512 185 / 334;
+  // 3 x 2500 tokens (236 workgroups): W = 0 42 / 30, W = 64 52 / 42;
+  // d = 128, 4 x 16K tokens: W = 0 456 / 467, W = 512 1114 / 935.
   const int rows = a.C * a.G;
+  constexpr bool kTwoPerCu = 2 * MainLds<T, D, DF>::bytes <= 160 * 1024;
+  const bool many = int64_t(a.nseg) * a.Hkv * a.nlayer > kSegCus;
   auto main = [&](int pass) {
-    if (rows <= 64) main_t<T, D, DF, 64, 4>(a, pass, s);
-    else if (rows <= 128) main_t<T, D, DF, 128, 8>(a, pass, s);
+    if constexpr (sizeof(T) == 4 || kTwoPerCu) {
+      if (rows <= 64 && (sizeof(T) == 4 || many)) {
+        main_t<T, D, DF, 64, 4>(a, pass, s);
+        return;
+      }
+    }
+    if (rows <= 128) main_t<T, D, DF, 128, 8>(a, pass, s);
     else main_t<T, D, DF, 256, 8>(a, pass, s);
   };
   if (a.gated) {  // the new tokens' cumulative log-gates, before any kernel reads them

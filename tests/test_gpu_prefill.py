@@ -231,3 +231,11 @@ def test_rows_per_pass(dtype, G, chunk):
     filled, and one row past), with and without a band."""
     case = Case([0, 5, 70], batch=2, Hq=2 * G, Hkv=2, d=128, Df=64, dtype=dtype, seed=22)
     _prefill_from_empty(case, [161, 95], chunk=chunk, label=f"G={G} chunk={chunk}")
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_rows_per_pass_many_workgroups(dtype):
+    """One query head per KV head at d = 64 in a launch of more workgroups than
+    the device has CUs (the 64-row passes also in bf16)."""
+    case = Case([0, 5, 64, 70] * 3, batch=4, Hq=4, Hkv=4, d=64, Df=64, dtype=dtype, seed=24)
+    _prefill_from_empty(case, [161, 95, 130, 200], label="many workgroups")
