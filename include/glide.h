@@ -164,17 +164,19 @@ size_t glide_state_bytes(const glide_config* cfg);
 /* Fills *out with the layout of layer `layer` (0 <= layer < cfg->n_layers). */
 glide_status glide_state_layout(const glide_config* cfg, int32_t layer, glide_layer_layout* out);
 
-/* Workspace bytes needed by glide_prefill for calls of max_total_tokens
- * packed tokens (any chunk size) and by glide_decode_step (any layer range);
- * at least 256.  Prefill takes one slot per layer of a launch (history rows
- * and per-segment state records) and batches as many layers per launch as
- * the given workspace holds, up to 64; this size holds as many as fit in
- * 1 GiB (at least one).  Decode uses the workspace only when a launch has
- * fewer (sequence, KV head) units than the device holds resident decode
- * workgroups in one round (two per compute unit: 512 on MI355X): it then
- * splits long windows (more than 256 tokens) over several workgroups, whose
- * partial results it holds.  The size bounds that for every call on any device (at most 1024
- * records; a call over any subset of the layers).  0 if cfg is invalid. */
+/* Workspace bytes that serve glide_prefill for every call of up to
+ * max_total_tokens packed tokens (any chunk size, so the size never falls as
+ * max_total_tokens grows) and glide_decode_step (any layer range); at least
+ * 256.  Prefill takes one slot per layer of a launch (history rows and
+ * per-segment state records) and batches as many layers per launch as the
+ * given workspace holds, up to 64; this size holds as many as fit in 1 GiB
+ * (at least one).  Decode uses the workspace only when a launch has fewer
+ * (sequence, KV head) units than the device holds resident decode workgroups
+ * in one round (two per compute unit: 512 on MI355X): it then splits long
+ * windows (more than 256 tokens) over several workgroups, whose partial
+ * results it holds.  The size bounds that for every call on any device (at
+ * most 1024 records; a call over any subset of the layers).  0 if cfg is
+ * invalid. */
 size_t glide_workspace_bytes(const glide_config* cfg, int64_t max_total_tokens);
 
 /* Zeroes the whole state: S = 0, z = 0 (S_0, Z_0 of the Sec. II-B
@@ -201,7 +203,7 @@ glide_status glide_state_init(const glide_config* cfg, void* state, size_t state
  *          sequence's new q rows must span less than 2 GiB (T_b * Hq * d *
  *          element bytes < 2^31, else GLIDE_ERR_UNSUPPORTED)
  *   out    device [n_layers][T][Hq][d]
- *   workspace device, >= glide_workspace_bytes(cfg, T)
+ *   workspace device, >= glide_workspace_bytes(cfg, T') of any T' >= T
  * Element types follow cfg->dtype; device pointers 16-byte aligned. */
 glide_status glide_prefill(const glide_config* cfg, void* state, size_t state_bytes,
                            int32_t layer0, int32_t n_layers, const void* phi_w,

@@ -94,9 +94,14 @@ int32_t max_window(const glide_config* c) {
   return w;
 }
 
-PrefillWorkspace prefill_ws(const glide_config* c, int64_t T, int32_t nl) {
+// One layer's slot for calls of T tokens in nseg segments at most, and for
+// those in launches of nl layers.
+PrefillWorkspace prefill_ws_of(const glide_config* c, int64_t T, int64_t nseg) {
   return prefill_workspace(T, c->batch, c->n_kv_heads, c->head_dim, c->feat_dim, esize(c), max_window(c),
-                           linear_on(c), nl, gated_on(c));
+                           linear_on(c), nseg, gated_on(c));
+}
+PrefillWorkspace prefill_ws(const glide_config* c, int64_t T, int32_t nl) {
+  return prefill_ws_of(c, T, segments(T, c->n_kv_heads, nl));
 }
 
 // Resident decode workgroups of one round on the current device:
@@ -197,6 +202,18 @@ size_t decode_ws(const glide_config* c) {
   if (!any) return 0;
   return size_t(align256(std::min<int64_t>(wgs, kMaxDecodeSlots) *
                          part_floats(c->n_q_heads / c->n_kv_heads, c->head_dim) * 4));
+}
+
+// What a prefill call of T tokens asks of its workspace: as many layers per
+// launch as fit in the budget (at least one), without short segments.
+size_t prefill_need(const glide_config* c, int64_t T) {
+  size_t pre = 0;
+  if (T > 0) {
+    auto slot_of = [&](int32_t nl) { return prefill_ws(c, T, nl).slot; };
+    const int32_t nl = prefill_layers_per_launch(c->n_layers, kPrefillWsBudget, slot_of);
+    pre = std::max(slot_of(1), size_t(nl) * (nl > 0 ? slot_of(nl) : 0));
+  }
+  return std::max(size_t(256), std::max(pre, decode_ws(c)));
 }
 
 // Decode-style launch descriptor of layers [layer0, layer0 + n): per launch
@@ -327,12 +344,18 @@ glide_status glide_state_layout(const glide_config* cfg, int32_t layer, glide_la
 
 size_t glide_workspace_bytes(const glide_config* cfg, int64_t max_total_tokens) {
   if (check_cfg(cfg) != GLIDE_OK || max_total_tokens < 0) return 0;
+  // Enough for every call of at most that many tokens.  A smaller call can
+  // have more segments, and more layers in the budget, so its prefill_need is
+  // not always the smaller one: most_segments covers its slots, and its
+  // layers per launch are at most those whose slots for one token fit.
   size_t pre = 0;
   if (max_total_tokens > 0) {
-    // as many layers per launch as fit in the budget (at least one)
-    auto slot_of = [&](int32_t nl) { return prefill_ws(cfg, max_total_tokens, nl).slot; };
-    const int32_t nl = prefill_layers_per_launch(cfg->n_layers, kPrefillWsBudget, slot_of);
-    pre = std::max(slot_of(1), size_t(nl) * (nl > 0 ? slot_of(nl) : 0));
+    const int64_t T = max_total_tokens;
+    auto slot_of = [&](int32_t nl) { return prefill_ws_of(cfg, T, most_segments(T, cfg->n_kv_heads, nl)).slot; };
+    auto least = [&](int32_t nl) { return prefill_ws(cfg, 1, nl).slot; };
+    const int32_t most = prefill_layers_per_launch(cfg->n_layers, kPrefillWsBudget, least);
+    for (int32_t nl = 1; nl <= most; ++nl) pre = std::max(pre, size_t(nl) * slot_of(nl));
+    pre = std::max(slot_of(1), std::min(kPrefillWsBudget, pre));
   }
   return std::max(size_t(256), std::max(pre, decode_ws(cfg)));
 }
@@ -436,8 +459,7 @@ glide_status glide_prefill(const glide_config* cfg, void* state, size_t state_by
       return GLIDE_ERR_UNSUPPORTED;
   if (chunk == 0) chunk = 64;
   if (chunk < 32 || chunk > 256 || chunk % 32) return GLIDE_ERR_INVALID;
-  const size_t need = glide_workspace_bytes(cfg, total_tokens);
-  if (workspace_bytes < need) return GLIDE_ERR_SIZE;
+  if (workspace_bytes < prefill_need(cfg, total_tokens)) return GLIDE_ERR_SIZE;
   if (!workspace) return GLIDE_ERR_NULL;
   if (!aligned(workspace, 256)) return GLIDE_ERR_ALIGN;
   if (total_tokens == 0) return GLIDE_OK;
@@ -451,8 +473,16 @@ glide_status glide_prefill(const glide_config* cfg, void* state, size_t state_by
   // that many layers) as the caller's workspace holds
   auto slot_of = [&](int32_t nl) { return prefill_ws(cfg, T, nl).slot; };
   const int32_t per_launch = std::max(1, prefill_layers_per_launch(n_layers, workspace_bytes, slot_of));
-  const PrefillWorkspace w = prefill_ws(cfg, T, per_launch);
-  const int32_t seg_len = chunk * segment_chunks(T, Hkv, chunk, per_launch);
+  PrefillWorkspace w = prefill_ws(cfg, T, per_launch);
+  int32_t seg_len = chunk * segment_chunks(T, Hkv, chunk, per_launch);
+  const int32_t short_len = chunk * short_segment_chunks(T, Hkv, chunk, per_launch);
+  if (short_len > 0) {
+    const PrefillWorkspace ws = prefill_ws_of(cfg, T, T / short_len);
+    if (size_t(per_launch) * ws.slot <= workspace_bytes) {
+      w = ws;
+      seg_len = short_len;
+    }
+  }
 
   PrefillArgs a;
   memset(&a, 0, sizeof(a));

@@ -702,44 +702,87 @@ struct PrefillArgs {
 };
 static_assert(sizeof(PrefillArgs) <= 4096, "kernel argument block");
 
-// Segments hold at least kMinSegTokens tokens, which bounds the records.
+// Segments hold at least kMinSegTokens tokens.
 constexpr int kMinSegTokens = 64;
 
 // Chunks per prefill segment, for a launch of nl layers: about kSegRounds
 // workgroups per CU over the launch's (segment, KV head, layer) grid when the
 // call is large enough (longer segments amortise each workgroup's start, the
 // state load, over more chunks; several rounds keep the CUs evenly loaded
-// across layers of different windows), at most 16 chunks walked in order by
-// one workgroup.  A smaller call takes the shorter time by a simple model of
-// the main kernel: rounds of one workgroup per CU, each its chunks plus a
-// start worth 0.4 of a chunk, over segments of about 128 tokens or half
-// as many (never under kMinSegTokens).  512 tokens x 4 heads (fp32, W = 64):
-// one round of one chunk in place of two, 60 -> 41.7 us per call; 8 x 301 ..
-// 2047 tokens x 8 heads (W = 1000): five rounds of one in place of three of
-// two, 430 -> 413 us.
+// across layers of different windows), at most kMaxSegChunks chunks walked in
+// order by one workgroup; about 128 tokens in a smaller call.
 constexpr int kSegRounds = 8;
 constexpr int kSegCus = 256;
+constexpr int kMaxSegChunks = 16;
+inline int32_t min_segment_chunks(int32_t chunk) { return (2 * kMinSegTokens + chunk - 1) / chunk; }
 inline int32_t segment_chunks(int64_t T, int Hkv, int32_t chunk, int32_t nl) {
   const int64_t fill = T * Hkv * nl / (int64_t(chunk) * kSegCus * kSegRounds);
-  const int32_t lo = (2 * kMinSegTokens + chunk - 1) / chunk;
-  if (fill > lo) return int32_t(fill < 16 ? fill : 16);
-  const int32_t half = (kMinSegTokens + chunk - 1) / chunk;
+  const int32_t lo = min_segment_chunks(chunk);
+  if (fill > lo) return int32_t(fill < kMaxSegChunks ? fill : kMaxSegChunks);
+  return lo;
+}
+
+// Half as many chunks (never under kMinSegTokens tokens) where segment_chunks
+// gives its least and a simple model of the main kernel says that they end
+// sooner: rounds of one workgroup per CU, each its chunks plus a start worth
+// 0.4 of a chunk; 0 where they do not.  512 tokens x 4 heads (fp32, W = 64):
+// one round of one chunk in place of two, 60 -> 41.7 us per call; 8 x 301 ..
+// 2047 tokens x 8 heads (W = 1000): five rounds of one in place of three of
+// two, 430 -> 413 us.  A call takes them only where the records of its shorter
+// segments fit the workspace it was given (kShortWgs: what the reported size
+// has room for).
+constexpr int kShortWgs = 9 * kSegCus;
+inline int32_t short_segment_chunks(int64_t T, int Hkv, int32_t chunk, int32_t nl) {
+  const int32_t lo = min_segment_chunks(chunk), half = (kMinSegTokens + chunk - 1) / chunk;
+  if (half >= lo || segment_chunks(T, Hkv, chunk, nl) != lo) return 0;
   auto cost = [&](int32_t n) {  // in tenths of a chunk's time
     const int64_t wgs = (T + int64_t(n) * chunk - 1) / (int64_t(n) * chunk) * Hkv * nl;
     return (wgs + kSegCus - 1) / kSegCus * (10 * n + 4);
   };
-  return half < lo && cost(half) < cost(lo) ? half : lo;
+  return cost(half) < cost(lo) ? half : 0;
+}
+
+// Segments of a call of T tokens (beyond one per sequence), at most: the
+// shortest that segment_chunks gives over the legal chunks.
+inline int64_t segments(int64_t T, int Hkv, int32_t nl) {
+  int64_t n = 0;
+  for (int32_t c = 32; c <= 256; c += 32) {
+    const int64_t x = T / (int64_t(c) * segment_chunks(T, Hkv, c, nl));
+    n = x > n ? x : n;
+  }
+  return n;
+}
+
+// The most segments of any call of at most T tokens (never less for a larger
+// T, unlike segments(), which falls wherever segments become a chunk longer):
+// over every chunk and segment length, those of the longest such call; and the
+// short segments that fit kShortWgs workgroups.
+inline int64_t most_segments(int64_t T, int Hkv, int32_t nl) {
+  const int64_t heads = int64_t(Hkv) * nl;
+  int64_t n = T / kMinSegTokens < kShortWgs / heads ? T / kMinSegTokens : kShortWgs / heads;
+  for (int32_t c = 32; c <= 256; c += 32) {
+    const int64_t step = int64_t(c) * kSegCus * kSegRounds;  // tokens x heads per chunk of a segment
+    const int32_t lo = min_segment_chunks(c);
+    for (int32_t m = lo; m <= kMaxSegChunks; ++m) {
+      if (m > lo && (m * step + heads - 1) / heads > T) break;  // no call this small has m chunks
+      int64_t last = m < kMaxSegChunks ? ((m + 1) * step + heads - 1) / heads - 1 : T;
+      last = last < T ? last : T;
+      const int64_t x = last / (int64_t(c) * m);
+      n = x > n ? x : n;
+    }
+  }
+  return n;
 }
 
 struct PrefillWorkspace {
   size_t hk, hv, seg, hg, gc, slot;  // offsets within a slot, and the slot's bytes
 };
 
-// One layer's slot for calls of T tokens in launches of nl layers: the
-// records bound takes the shortest segment any legal chunk gives for T.
-// Gated: the history tokens' and the new tokens' cumulative log-gates (fp64).
+// One layer's slot for calls of T tokens in nseg segments at most (and one
+// more per sequence).  Gated: the history tokens' and the new tokens'
+// cumulative log-gates (fp64).
 inline PrefillWorkspace prefill_workspace(int64_t T, int B, int Hkv, int d, int Df, int esize, int Wcap,
-                                          bool linear, int32_t nl, bool gated = false) {
+                                          bool linear, int64_t nseg, bool gated = false) {
   PrefillWorkspace w;
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -747,14 +790,9 @@ inline PrefillWorkspace prefill_workspace(int64_t T, int B, int Hkv, int d, int 
     off += size_t(align256(int64_t(bytes)));
     return o;
   };
-  int64_t seg_min = INT64_MAX;
-  for (int32_t c = 32; c <= 256; c += 32) {
-    const int64_t sl = int64_t(c) * segment_chunks(T, Hkv, c, nl);
-    seg_min = sl < seg_min ? sl : seg_min;
-  }
   w.hk = take(size_t(B) * Hkv * Wcap * d * esize);
   w.hv = take(size_t(B) * Hkv * Wcap * d * esize);
-  w.seg = take(linear ? (size_t(T / seg_min) + B) * Hkv * (size_t(Df) * d + Df) * 4 : 0);
+  w.seg = take(linear ? (size_t(nseg) + B) * Hkv * (size_t(Df) * d + Df) * 4 : 0);
   w.hg = take(gated ? size_t(B) * Hkv * Wcap * 8 : 0);
   w.gc = take(gated ? size_t(T) * Hkv * 8 : 0);
   w.slot = off;

@@ -107,9 +107,10 @@ class Case:
         torch.cuda.synchronize()
         return torch.stack(outs, 2).cpu()
 
-    def prefill(self, state, q, k, v, starts, lens, chunk=0, gates=None):
+    def prefill(self, state, q, k, v, starts, lens, chunk=0, gates=None, ws_bytes=None):
         """Prefill tokens [starts[b], starts[b] + lens[b]) of every sequence (one
-        call over all layers); returns out [L][B] list of [lens[b]][Hq][d] (CPU)."""
+        call over all layers, in a workspace of its own size or of ws_bytes);
+        returns out [L][B] list of [lens[b]][Hq][d] (CPU)."""
         cu = [0]
         for n in lens:
             cu.append(cu[-1] + n)
@@ -120,7 +121,8 @@ class Case:
         gp = None if gates is None else torch.cat([gates[:, b, s:s + n] for b, (s, n) in enumerate(zip(starts, lens))],
                                                   1).contiguous().cuda()
         out = torch.full((self.L, T, self.Hq, self.d), float("nan"), dtype=self.dtype, device="cuda")
-        ws = self.g.new_workspace(max(T, 1))
+        ws = (self.g.new_workspace(max(T, 1)) if ws_bytes is None
+              else torch.empty(ws_bytes, dtype=torch.uint8, device="cuda"))
         self.g.prefill(state, self.phi_w.cuda(), qp.cuda(), kp.cuda(), vp.cuda(), cu, out, ws, chunk=chunk,
                        log_gates=gp)
         torch.cuda.synchronize()

@@ -251,6 +251,35 @@ def _prefill(g, cu, total, chunk=0, ws_bytes=None, state=256, ptrs=(4096,) * 6, 
                                P[5], ws_bytes, None)
 
 
+@pytest.mark.parametrize("kw", [
+    dict(n_layers=1, batch=1, n_q_heads=32, n_kv_heads=8, feat_dim=128, windows=[512]),
+    dict(n_layers=1, batch=1, n_q_heads=32, n_kv_heads=8, feat_dim=128, windows=[0]),
+    dict(n_layers=1, batch=8, n_q_heads=32, n_kv_heads=8, feat_dim=128, windows=[1000]),
+    dict(n_layers=1, batch=8, n_q_heads=64, n_kv_heads=8, feat_dim=128, windows=[8191], gated=True),
+    dict(n_layers=1, batch=1, n_q_heads=4, n_kv_heads=4, head_dim=64, windows=[64], dtype=torch.float32),
+    dict(n_layers=1, batch=2, n_q_heads=300, n_kv_heads=300, head_dim=64, windows=[64]),
+    dict(n_layers=32, batch=1, n_q_heads=32, n_kv_heads=8, feat_dim=128, windows=[16 * (l + 1) for l in range(32)]),
+    dict(n_layers=80, batch=8, n_q_heads=64, n_kv_heads=8, feat_dim=128, windows=[50 * (l + 1) for l in range(80)]),
+])
+def test_workspace_serves_smaller_calls(kw):
+    """A workspace of workspace_bytes(T) serves every call of t <= T tokens:
+    the size never falls as T grows, and prefill asks for no more than it for
+    any smaller call (one layer or the stack).  Its workspace pointer is NULL
+    here, which is looked at after the size: -1, and no HIP call, where the
+    size is enough."""
+    g = mk(**kw)
+    B = kw["batch"]
+    ts = sorted({t + o for t in range(16, 60000, 48) for o in (-1, 0, 1)} | {64000 + 511 * i for i in range(100)})
+    sizes = [g.workspace_bytes(t) for t in ts]
+    assert all(a <= b for a, b in zip(sizes, sizes[1:]))
+    caps = [2049, 8192, 16384, 18448, 20000, 32768, 49152, 100000]
+    for cap in caps:
+        have = g.workspace_bytes(cap)
+        for t in range(1, cap + 1, 37):
+            assert _prefill(g, [t * b // B for b in range(B + 1)], t, ws_bytes=have, ptrs=(4096,) * 5 + (None,),
+                            gates=8192 if kw.get("gated") else None) == -1, (cap, t)
+
+
 def test_prefill_argument_errors():
     g = mk()
     assert _prefill(g, [0, 5, 3], 3) == -2              # decreasing

@@ -1,4 +1,6 @@
 """GPU parity of glide_prefill against the CPU oracle (through the C ABI)."""
+import ctypes
+
 import pytest
 import torch
 
@@ -239,3 +241,36 @@ def test_rows_per_pass_many_workgroups(dtype):
     the device has CUs (the 64-row passes also in bf16)."""
     case = Case([0, 5, 64, 70] * 3, batch=4, Hq=4, Hkv=4, d=64, Df=64, dtype=dtype, seed=24)
     _prefill_from_empty(case, [161, 95, 130, 200], label="many workgroups")
+
+
+def _least_workspace(case, T):
+    """The least workspace size that prefill accepts for T tokens (its NULL
+    pointer is looked at after the size: -1 and no HIP call where it is enough)."""
+    def ok(n):
+        P = ctypes.c_void_p(4096)
+        cu = (ctypes.c_int32 * (case.B + 1))(*([0] * case.B + [T]))
+        return case.g.lib.glide_prefill(ctypes.byref(case.g.cfg), ctypes.c_void_p(256), case.g.state_bytes(), 0, case.L,
+                                        P, P, P, P, None, cu, T, 0, P, None, n, None) == -1
+    lo, hi = 0, case.g.workspace_bytes(T)
+    assert ok(hi) and not ok(lo)
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (lo, mid) if ok(mid) else (mid, hi)
+    return hi
+
+
+@pytest.mark.parametrize("size", ["least", "own", "larger"])
+@pytest.mark.parametrize("windows", [[64], [0, 70]])
+def test_workspace_of_another_size(windows, size):
+    """The same call in the least workspace that is accepted (which has no room
+    for the records of short segments), in its own, and in one made for more
+    tokens."""
+    case = Case(windows, batch=1, Hq=4, Hkv=4, d=64, Df=64, dtype=torch.float32, seed=26)
+    T = 500
+    n = {"least": _least_workspace(case, T), "own": case.g.workspace_bytes(T), "larger": case.g.workspace_bytes(4 * T)}[size]
+    assert size != "least" or n < case.g.workspace_bytes(T)
+    q, k, v = case.tokens(T)
+    st = case.new_state()
+    outs = case.prefill(st, q, k, v, [0], [T], ws_bytes=n)
+    case.check_prefill(outs, q, k, v, [0], [T], f"workspace {size}")
+    case.check_state(st, k, v, [T], f"workspace {size}")
