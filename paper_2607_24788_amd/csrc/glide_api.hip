@@ -216,6 +216,26 @@ size_t prefill_need(const glide_config* c, int64_t T) {
   return std::max(size_t(256), std::max(pre, decode_ws(c)));
 }
 
+// Tokens of a prefill call's short segments where they are expected to end
+// sooner than the least that segment_chunks gives; 0: not short.
+int32_t short_segment_tokens(const glide_config* c, int32_t layer0, int32_t n_layers, const int32_t* cu, int32_t chunk,
+                             int32_t per_launch) {
+  const int32_t n_half = (kMinSegTokens + chunk - 1) / chunk, n = min_segment_chunks(chunk);
+  if (n_half >= n || segment_chunks(cu[c->batch], c->n_kv_heads, chunk, per_launch) != n) return 0;
+  auto workgroups = [&](int32_t chunks) {
+    int64_t segs = 0;
+    for (int32_t b = 0; b < c->batch; ++b) segs += (cu[b + 1] - cu[b] + chunks * chunk - 1) / (chunks * chunk);
+    return segs * c->n_kv_heads * per_launch;
+  };
+  const int64_t wgs = workgroups(n_half);
+  if (wgs > kShortWgs) return 0;
+  double chunk_us = 0;  // mean over the layers
+  for (int32_t l = layer0; l < layer0 + n_layers; ++l)
+    chunk_us += prefill_chunk_us(chunk, c->n_q_heads / c->n_kv_heads, c->windows[l], c->head_dim,
+                                 c->dtype == GLIDE_F32) / n_layers;
+  return segments_us(wgs, n_half, chunk_us) < segments_us(workgroups(n), n, chunk_us) ? n_half * chunk : 0;
+}
+
 // Decode-style launch descriptor of layers [layer0, layer0 + n): per launch
 // group of at most kMaxLayersPerLaunch layers, ordered by decreasing window
 // (the hardware dispatcher then hands out the longest streams first).
@@ -475,12 +495,12 @@ glide_status glide_prefill(const glide_config* cfg, void* state, size_t state_by
   const int32_t per_launch = std::max(1, prefill_layers_per_launch(n_layers, workspace_bytes, slot_of));
   PrefillWorkspace w = prefill_ws(cfg, T, per_launch);
   int32_t seg_len = chunk * segment_chunks(T, Hkv, chunk, per_launch);
-  const int32_t short_len = chunk * short_segment_chunks(T, Hkv, chunk, per_launch);
-  if (short_len > 0) {
-    const PrefillWorkspace ws = prefill_ws_of(cfg, T, T / short_len);
+  const int32_t half = short_segment_tokens(cfg, layer0, n_layers, cu_seqlens_host, chunk, per_launch);
+  if (half > 0) {
+    const PrefillWorkspace ws = prefill_ws_of(cfg, T, T / half);
     if (size_t(per_launch) * ws.slot <= workspace_bytes) {
       w = ws;
-      seg_len = short_len;
+      seg_len = half;
     }
   }
 

@@ -722,24 +722,28 @@ inline int32_t segment_chunks(int64_t T, int Hkv, int32_t chunk, int32_t nl) {
   return lo;
 }
 
-// Half as many chunks (never under kMinSegTokens tokens) where segment_chunks
-// gives its least and a simple model of the main kernel says that they end
-// sooner: rounds of one workgroup per CU, each its chunks plus a start worth
-// 0.4 of a chunk; 0 where they do not.  512 tokens x 4 heads (fp32, W = 64):
-// one round of one chunk in place of two, 60 -> 41.7 us per call; 8 x 301 ..
-// 2047 tokens x 8 heads (W = 1000): five rounds of one in place of three of
-// two, 430 -> 413 us.  A call takes them only where the records of its shorter
-// segments fit the workspace it was given (kShortWgs: what the reported size
-// has room for).
+// Short segments, half as many chunks (never under kMinSegTokens tokens), where
+// segment_chunks gives its least and they end sooner by a model of the call in
+// microseconds: rounds of one workgroup per CU, each a start and its chunks
+// (below), and 0.03 per segment and head for the records.  Fitted to 2073
+// calls of 128 .. 16000 tokens timed both ways (fresh and continuing; d = 64
+// and 128; 1, 4 and 8 query heads per KV head; fp32 and bf16; W = 0 .. 4096):
+// on average 0.7% over the better of the two, and at most 2.8% over the longer
+// segments; always the longer ones: 14% over.  512 tokens x 4 heads (fp32,
+// W = 64), one round of one chunk in place of two: 60 -> 41.7 us per call;
+// 10000 tokens x 8 heads, five rounds of one or three of two: W = 0 161 / 129
+// us, W = 2048 482 / 522 us.  A call takes them only up to kShortWgs workgroups
+// (what the reported workspace has room for) and where the records fit the
+// workspace it was given.
 constexpr int kShortWgs = 9 * kSegCus;
-inline int32_t short_segment_chunks(int64_t T, int Hkv, int32_t chunk, int32_t nl) {
-  const int32_t lo = min_segment_chunks(chunk), half = (kMinSegTokens + chunk - 1) / chunk;
-  if (half >= lo || segment_chunks(T, Hkv, chunk, nl) != lo) return 0;
-  auto cost = [&](int32_t n) {  // in tenths of a chunk's time
-    const int64_t wgs = (T + int64_t(n) * chunk - 1) / (int64_t(n) * chunk) * Hkv * nl;
-    return (wgs + kSegCus - 1) / kSegCus * (10 * n + 4);
-  };
-  return cost(half) < cost(lo) ? half : 0;
+inline double segments_us(int64_t wgs, int32_t chunks, double chunk_us) {
+  return double((wgs + kSegCus - 1) / kSegCus) * (8 + chunks * chunk_us) + 0.03 * double(wgs);
+}
+// One chunk of C tokens x G heads in a layer of window W: per pass of 256 rows
+// the linear part, the band's fixed part and a microsecond per 32 keys.
+inline double prefill_chunk_us(int32_t C, int32_t G, int32_t W, int d, bool fp32) {
+  const double us = double((C * G + 255) / 256) * (8 + (W > 0 ? 4 : 0) + W / 32.0);
+  return us * (fp32 ? 4 : 1) / (d == 64 ? 3 : 1);
 }
 
 // Segments of a call of T tokens (beyond one per sequence), at most: the
