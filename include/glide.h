@@ -124,8 +124,9 @@ typedef struct {
  * blob's start).  Layout per layer l, every section 256-byte aligned:
  *   pos   int64 [B][Hkv]          p: tokens consumed by sequence b (equal over Hkv)
  *   nf    int64 [B][Hkv]          tokens folded into S and z (see below)
- *   cnt   int32 [B][Hkv]          decode bookkeeping: pieces of a split unit
- *                                 done in the current step; 0 between calls
+ *   cnt   int32 [B][Hkv]          bookkeeping within a call: workgroups of a
+ *                                 unit that are done; 0 between calls (decode
+ *                                 needs it 0; prefill clears it)
  *   S     fp32  [B][Hkv][Df][d]   sum of phi(k_j)^T v_j over tokens j < nf
  *   z     fp32  [B][Hkv][Df]      sum of phi(k_j) over the same tokens
  *   kring dtype [B][Hkv][R*d]     keys, token j in slot s = j mod R

@@ -389,13 +389,18 @@ __device__ __forceinline__ void phi_slab(const WfCols<T, D, DF, kLds>& wf, const
 
 // ---------------------------------------------------------------------------
 // begin: workgroup 0 of each (sequence, KV head) folds its pending tokens (it
-// writes S, z and nf, which no other workgroup here reads); the others gather
-// the history tokens [h0, p0) of a continuing prefill, ring ->
+// writes S, z and nf, which no other workgroup here reads) and clears the
+// unit's count for `end`, whatever the caller's state held there; the others
+// gather the history tokens [h0, p0) of a continuing prefill, ring ->
 // [b][g][Wcap][d].
 template <typename T, int D, int DF>
 __global__ __launch_bounds__(kThreads) void prefill_begin(PrefillArgs a) {
   const int bl = blockIdx.y, g = int(blockIdx.z) % a.Hkv;
   const LayerView L = layer_view(a, int(blockIdx.z) / a.Hkv);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    const LayerSections sec = layer_sections(a.B, a.Hkv, D, DF, L.R, sizeof(T));
+    reinterpret_cast<int*>(L.base + sec.cnt)[int64_t(a.seq0 + bl) * a.Hkv + g] = 0;
+  }
   if (L.W == 0) return;
   if (blockIdx.x == 0) {
     if (a.linear && L.Wd > 0)
@@ -1673,8 +1678,9 @@ void prefill_main(PrefillArgs a) {
 // Then advance: pos += T_b; the scan left S, z = the sums over tokens
 // [0, max(0, pos - Wd)), nothing pending.  Every workgroup of a unit reads the
 // old pos, so the last of them to finish writes the new one: each waits for
-// its own reads, then adds one to the unit's count (zero between calls; the
-// last resets it).
+// its own reads, then adds one to the unit's count (cleared by `begin`, which
+// runs in every launch with a window, the only ones of several workgroups per
+// unit; the last resets it).
 template <typename T, int D, int DF>
 __device__ __forceinline__ void ring_fill(const PrefillArgs& a, const LayerView& L, const SeqRows<T, D>& sr, int bl,
                                           int g) {

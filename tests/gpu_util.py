@@ -205,6 +205,7 @@ class Case:
             views = self.g.layer_views(state, l)
             o = self.oracle(l)
             W, R = self.windows[l], views["ring_slots"]
+            assert int(views["cnt"].abs().max()) == 0, f"{label} cnt layer {l} not 0 between calls"
             for b, p in enumerate(positions):
                 assert int(views["pos"][b].min()) == p and int(views["pos"][b].max()) == p, \
                     f"{label} pos layer {l} seq {b}"

@@ -301,3 +301,21 @@ def test_segment_tokens(lens, W, d, tokens):
     n = (ws.numel() - start) // rec
     written = (ws[start:start + n * rec].view(n, rec) != 0xff).any(1)
     assert int(written.sum()) == sum(-(-x // tokens) for x in lens)
+
+
+@pytest.mark.parametrize("windows", [[70], [0, 70], [0]])
+@pytest.mark.parametrize("cnt", [-1, 1, 3])
+def test_prefill_ignores_the_count(windows, cnt):
+    """A state whose cnt section a caller left non-zero: prefill works from
+    pos, nf, S, z and the rings alone, and leaves cnt 0 wherever it counts."""
+    case = Case(windows, batch=2, Hq=4, Hkv=2, d=64, Df=64, dtype=torch.bfloat16, seed=28)
+    q, k, v = case.tokens(250)
+    st = case.new_state()
+    for s, n in (([0, 0], [200, 90]), ([200, 90], [50, 33])):
+        for l in range(case.L):
+            case.g.layer_views(st, l)["cnt"].fill_(cnt)
+        outs = case.prefill(st, q, k, v, s, n)
+        case.check_prefill(outs, q, k, v, s, n, f"cnt {cnt}")
+        if windows == [0]:
+            case.g.layer_views(st, 0)["cnt"].zero_()
+        case.check_state(st, k, v, [a + b for a, b in zip(s, n)], f"cnt {cnt}")
