@@ -811,6 +811,11 @@ void prefill_main(PrefillArgs a) {
   const bool qneg = a.tau < 0.f;
   const float sc2 = fmaxf(fabsf(a.tau) * kLog2e, 1e-30f);
   const float inv_sc2 = 1.f / sc2;
+  // the band stages tile n + 1 at tile n's start (kEarly), and reads its K
+  // fragments behind tile n's P V where the registers hold K and V fragments at
+  // once (kAhead)
+  constexpr bool kEarly = sizeof(T) == 2;
+  constexpr bool kAhead = sizeof(T) == 2 && !GATED && (PASS != 0 || DF >= D || QT == 1);
   constexpr bool kOnesSum = sizeof(T) == 2;  // the band's row sums on the matrix cores
   const T* Q = static_cast<const T*>(L.q);
   T* O = static_cast<T*>(L.out);
@@ -955,7 +960,10 @@ void prefill_main(PrefillArgs a) {
       // and merges them, which waits for the loads here: done for every
       // history tile it put the memory latency into each of them (8 sequences
       // of 16K tokens extended by 301 .. 2047, W = 1000: 551 us per call
-      // against 450).
+      // against 450).  kPick: the rows' base, size and pitch are picked in
+      // scalar registers, not by a branch: where vector registers are short
+      // (fp32, d = 128: W = 2048, 6577 us by the branch, 6017 picked; the bf16
+      // calls, short of scalar ones, are 1-2% faster with the branch).
 #pragma unroll
       for (int u = 0; u < SPT; ++u) {
         const int id = tid + u * NTH, srr = id / CPR, sch = id - srr * CPR;
@@ -974,7 +982,21 @@ void prefill_main(PrefillArgs a) {
           bload_frag(fk, make_rsrc(sr.kh, hb), oh);
           bload_frag(fv, make_rsrc(sr.vh, hb), oh);
         };
-        if (jn + 31 < 0) {  // (uniform)
+        constexpr bool kPick = sizeof(T) == 4 && D == 128;
+        if constexpr (kPick) {
+          const bool hist = jn + 31 < 0;
+          const uint32_t nb = hist ? uint32_t(nh) * D * sizeof(T) : nbytes, rp = hist ? uint32_t(D * sizeof(T)) : rowb;
+          const int jr = (hist ? jn + nh : jn) + srr;
+          const uint32_t on = ok && jr >= 0 ? uint32_t(jr) * rp + cb : kOOB;
+          bload_frag(sk[u], make_rsrc(hist ? sr.kh : sr.kin + (int64_t(sr.start) * a.Hkv + g) * D, nb), on);
+          bload_frag(sv[u], make_rsrc(hist ? sr.vh : sr.vin + (int64_t(sr.start) * a.Hkv + g) * D, nb), on);
+          if (!hist && jn < 0) {
+            Frag<T> hk, hv;
+            old_rows(hk, hv);
+            sk[u] = frag_or(sk[u], hk);
+            sv[u] = frag_or(sv[u], hv);
+          }
+        } else if (jn + 31 < 0) {  // (uniform)
           old_rows(sk[u], sv[u]);
         } else {
           new_rows(sk[u], sv[u]);
@@ -999,13 +1021,16 @@ void prefill_main(PrefillArgs a) {
       }
     }
   };
-  // (with a band, the first slab of delayed keys is loaded after it: its
-  // registers are not held through the band loop.  Without one (kNoBand) it
-  // is loaded with the queries, a whole pass ahead of their use.)
-  constexpr bool kNoBand = PASS == 1;
+  // With a band, the first slab of delayed keys is loaded after it: its
+  // registers are not held through the band loop.  Without one (kPassAhead) it
+  // is loaded with the queries, a whole pass ahead of their use.  256-row passes
+  // in fp32 have the registers for that at d = Df = 64 only: held a pass ahead
+  // at d = 128 the rows spilled (4 x 4096 tokens, Df = 128, W = 0: 1002 us per
+  // call against 764; form 1 at W = 512: 2402 against 2168).
+  constexpr bool kPassAhead = PASS == 1 && (sizeof(T) == 2 || QT == 1 || (D == 64 && DF == 64));
   auto prefetch = [&]() {
     load_q();  // the band's queries, then the feature map's input
-    if constexpr (kNoBand) load_slab(t0, nk, 0);
+    if constexpr (kPassAhead) load_slab(t0, nk, 0);
     else if (W > 0) fetch(0);
   };
 
@@ -1070,7 +1095,7 @@ void prefill_main(PrefillArgs a) {
     if (W > 0) {
       refresh();
       store(0);  // tile 0 was fetched with the pass's other prefetches
-      if (ntile > 1) fetch(1);
+      if (kEarly && ntile > 1) fetch(1);
       if (qneg) {
 #pragma unroll
         for (int qt = 0; qt < QT; ++qt)
@@ -1097,9 +1122,12 @@ void prefill_main(PrefillArgs a) {
       // (59.1 -> 57.6 ms for 32 x 16K .. 32K tokens at W = 4096).  Two stages
       // are enough: tile n's V reads are done before its barrier, its K reads
       // before that, and the stage is written again after it (tile n + 2, in
-      // tile n + 1).  kAhead: where the registers hold K and V fragments at
-      // once (bf16, ungated); otherwise K is read at the tile's start.
-      constexpr bool kAhead = sizeof(T) == 2 && !GATED;
+      // tile n + 1).  Without kAhead (gated, and d = 128, Df = 64 in 256 rows, which
+      // spilled: 4 x 8192 tokens, W = 512, 613 us against 592, softmax map 648
+      // against 625) K is read at the tile's start.
+      // fp32 (not kEarly) fetches tile n + 1 at tile n's start and stages it at
+      // its end, with the barrier behind it: V need not be in registers by a
+      // barrier before P V, which spilled them.
       // scores: key row m of sub-tile t is key kb + 16t + m, so that a
       // 16-lane group's K reads cover 16 consecutive rows (distinct LDS
       // banks); lane (hq, lg) then holds the scores of keys 16t + 4lg + i,
@@ -1115,8 +1143,12 @@ void prefill_main(PrefillArgs a) {
       };
       if constexpr (kAhead) load_k(0);
       for (int n = 0; n < ntile; ++n) {
-        if (n + 1 < ntile) store(n + 1);
-        if (n + 2 < ntile) fetch(n + 2);
+        if constexpr (kEarly) {
+          if (n + 1 < ntile) store(n + 1);
+          if (n + 2 < ntile) fetch(n + 2);
+        } else {
+          if (n + 1 < ntile) fetch(n + 1);
+        }
         const T* vt = lds_fresh(static_cast<const T*>(bnd) + (n & 1) * BAND) + 32 * KROW;
         if constexpr (!kAhead) load_k(n);
         f32x4_t sc[QT][2];
@@ -1212,7 +1244,7 @@ void prefill_main(PrefillArgs a) {
             l_run[qt] += ps;
           }
         }
-        __syncthreads();  // tile n + 1 staged, tile n's fragments read
+        if constexpr (kEarly) __syncthreads();  // tile n + 1 staged, tile n's fragments read
         if constexpr (kAhead) {
           load_k(n + 1);  // (after the last tile: an old stage, never used)
           __builtin_amdgcn_sched_barrier(0);
@@ -1224,6 +1256,10 @@ void prefill_main(PrefillArgs a) {
         if constexpr (kOnesSum) {
 #pragma unroll
           for (int qt = 0; qt < QT; ++qt) lsum[qt] = mma(ones, pf[qt], lsum[qt]);
+        }
+        if constexpr (!kEarly) {
+          if (n + 1 < ntile) store(n + 1);
+          __syncthreads();
         }
       }
       if constexpr (kOnesSum) {
@@ -1238,7 +1274,7 @@ void prefill_main(PrefillArgs a) {
     //         -60 first (the band's terms rescaled to match) so that 2^-m
     //         stays finite; without a band (W = 0) m = 0.
     if (linear) {
-      if constexpr (!kNoBand) load_slab(t0, nk, 0);  // behind the feature map and the read-out
+      if constexpr (!kPassAhead) load_slab(t0, nk, 0);  // behind the feature map and the read-out
       float qscale[QT];
 #pragma unroll
       for (int qt = 0; qt < QT; ++qt) {
@@ -1492,7 +1528,7 @@ void prefill_main(PrefillArgs a) {
                                           nk - s0);
         }
         __syncthreads();
-        if constexpr (kNoBand) {
+        if constexpr (kPassAhead) {
           // Without a band nothing stands between the end of a pass and the
           // next one's feature map: its query rows and first slab are loaded
           // here, behind the masked block, the state update and the output
@@ -1643,7 +1679,7 @@ void prefill_main(PrefillArgs a) {
     // compiler's wait counts merge paths, and a path without these loads
     // would make the stores below wait for them).  After the last pass it
     // reloads that pass's rows: valid addresses, never waited for.
-    if constexpr (!kNoBand) {
+    if constexpr (!kPassAhead) {
       refresh();
       prefetch();
     }
