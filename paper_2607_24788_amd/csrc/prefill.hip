@@ -1842,7 +1842,11 @@ hipError_t layer_t(const PrefillArgs& a, hipStream_t s) {
   // Rows per pass, by a chunk's C * G rows.  64 rows on 4 waves multiply the
   // least padding, but the pass's work that is not per row (phi of the delayed
   // keys, the state update, staging) is then spread over 4 waves, not 8.  fp32
-  // pays most for padding (16 times the matrix cycles): always.  bf16: only
+  // pays most for padding (16 times the matrix cycles): always, but for the
+  // pass without a band where Wf stays in global memory and phi is most of the
+  // work (C = 64, G = 1, 4 x 4096 tokens, us per call, 64 rows against 128:
+  // d = Df = 128: W = 0 662 / 499, W = 64 867 / 949, W = 2048 2291 / 3173; d = 128,
+  // Df = 64: W = 0 244 / 288, W = 2048 1818 / 2704).  bf16: only
   // where two workgroups share a CU (LDS) and there are enough of them; one per
   // CU is better with 8 waves.  C = 64, G = 1, bf16, us per call, 64 rows
   // against 128: d = 64, 4 x 16K tokens: W = 0 99 / 121, W = 512 185 / 334;
@@ -1853,7 +1857,8 @@ hipError_t layer_t(const PrefillArgs& a, hipStream_t s) {
   const bool many = int64_t(a.nseg) * a.Hkv * a.nlayer > kSegCus;
   auto main = [&](int pass) {
     if constexpr (sizeof(T) == 4 || kTwoPerCu) {
-      if (rows <= 64 && (sizeof(T) == 4 || many)) {
+      const bool band = window && pass != 1;
+      if (rows <= 64 && (sizeof(T) == 4 ? band || MainLds<T, D, DF>::kWfLds : many)) {
         main_t<T, D, DF, 64, 4>(a, pass, s);
         return;
       }
