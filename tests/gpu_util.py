@@ -7,6 +7,8 @@ Tolerances (applied per tensor X, err = max |X_gpu - X_oracle|):
              err(S), err(z) <= 1e-2 * max |X_oracle|
   ring     : bit-exact (it is a copy of the inputs); pos exact.
 """
+import ctypes
+
 import numpy as np
 import torch
 
@@ -106,6 +108,25 @@ class Case:
             outs.append(o)
         torch.cuda.synchronize()
         return torch.stack(outs, 2).cpu()
+
+    def least_workspace(self, T, chunk=0):
+        """The least workspace size that prefill accepts for T tokens, which has
+        no room for the records of short segments: the main kernel's workgroups
+        then walk several chunks.  Probed with a NULL workspace, which is looked
+        at after the size (-1, and no HIP call, where that is enough)."""
+        P = ctypes.c_void_p(4096)
+        cu = (ctypes.c_int32 * (self.B + 1))(*([0] * self.B + [T]))
+
+        def ok(n):
+            return self.g.lib.glide_prefill(ctypes.byref(self.g.cfg), ctypes.c_void_p(256), self.g.state_bytes(), 0,
+                                            self.L, P, P, P, P, P if self.gated else None, cu, T, chunk, P, None, n,
+                                            None) == -1
+        lo, hi = 0, self.g.workspace_bytes(T)
+        assert ok(hi) and not ok(lo)
+        while hi - lo > 1:
+            mid = (lo + hi) // 2
+            lo, hi = (lo, mid) if ok(mid) else (mid, hi)
+        return hi
 
     def prefill(self, state, q, k, v, starts, lens, chunk=0, gates=None, ws_bytes=None):
         """Prefill tokens [starts[b], starts[b] + lens[b]) of every sequence (one

@@ -1,6 +1,4 @@
 """GPU parity of glide_prefill against the CPU oracle (through the C ABI)."""
-import ctypes
-
 import pytest
 import torch
 
@@ -217,13 +215,61 @@ def test_max_window():
     case.check_state(st, k, v, [140], "W=2^20")
 
 
+def _two_calls(case, n1, n2, chunk, walk, label, steps=0):
+    """A prefill from empty, decode steps, and a prefill from the reached state,
+    every output and the final state checked.  walk: in the least workspace (no
+    short segments), so that the workgroups walk from chunk to chunk."""
+    B = case.B
+    q, k, v = case.tokens(max(a + b for a, b in zip(n1, n2)) + steps)
+    gates = case.log_gates(q.shape[2]) if case.gated else None
+    st, pos = case.new_state(), [0] * B
+    for lens in (n1, n2):
+        ws = case.least_workspace(sum(lens), chunk) if walk else None
+        outs = case.prefill(st, q, k, v, pos, lens, chunk=chunk, gates=gates, ws_bytes=ws)
+        case.check_prefill(outs, q, k, v, pos, lens, f"{label} {lens}", gates=gates)
+        pos = [p + n for p, n in zip(pos, lens)]
+        if lens is n1:
+            for s in range(steps):
+                at = lambda x: torch.stack([x[:, b, pos[b] + s] for b in range(B)], 1).contiguous().cuda()  # noqa: E731
+                qs = at(q)
+                case.g.decode_step(st, case.phi_w.cuda(), qs, at(k), at(v), torch.empty_like(qs), case.ws,
+                                   log_gates=at(gates) if case.gated else None)
+            pos = [p + steps for p in pos]
+    case.check_state(st, k, v, pos, label, gates=gates)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("phi", [0, 1, 2])
 @pytest.mark.parametrize("G,chunk", [(1, 64), (4, 64), (8, 64), (4, 256)])
-def test_no_band(phi, G, chunk):
+def test_no_band(phi, G, chunk, dtype):
     """Calls over fully linear layers only (W = 0), whose passes load a pass
-    ahead: several passes per chunk, several slabs per chunk, ragged ends."""
-    case = Case([0, 0], batch=3, Hq=2 * G, Hkv=2, d=128, Df=128, dtype=torch.bfloat16, seed=23, phi=phi)
-    _prefill_from_empty(case, [321, 1, 64], chunk=chunk, label=f"no band phi={phi} G={G} chunk={chunk}")
+    ahead: several passes per chunk, several chunks per workgroup, ragged ends."""
+    case = Case([0, 0], batch=3, Hq=2 * G, Hkv=2, d=128, Df=128, dtype=dtype, seed=23, phi=phi)
+    _two_calls(case, [321, 1, 64], [65, 130, 0], chunk, True, f"no band phi={phi} G={G} chunk={chunk}")
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("opt", [dict(phi=1), dict(phi=2), dict(gated=True), dict(form=1), dict(form=2)], ids=str)
+@pytest.mark.parametrize("G,chunk,d,Df,walk", [
+    (4, 64, 128, 128, True), (8, 64, 128, 64, True), (8, 64, 64, 128, True),  # 256-row passes: one and two per chunk
+    (1, 64, 128, 128, False), (1, 64, 128, 64, True), (1, 32, 64, 64, True),  # 64-row passes (fp32)
+    (2, 64, 64, 128, True), (1, 96, 128, 128, True),                          # 128-row passes
+])
+def test_chunk_walk(dtype, opt, G, chunk, d, Df, walk):
+    """Every kind of main kernel carrying its state from chunk to chunk, then
+    from history rows and pending tokens (the hybrid forms' band-free pass
+    included, whose look-ahead crosses from history to new rows)."""
+    case = Case([0, 3, 40, 129], batch=2, Hq=2 * G, Hkv=2, d=d, Df=Df, dtype=dtype, seed=29, **opt)
+    _two_calls(case, [161, 61], [90, 200], chunk, walk, f"{opt} G={G} C={chunk} d={d}/{Df}", steps=5)
+
+
+@pytest.mark.parametrize("opt", [dict(), dict(phi=1), dict(phi=2), dict(gated=True), dict(form=1), dict(form=2)], ids=str)
+@pytest.mark.parametrize("windows", [[0] * 8, [0, 5, 64, 70] * 2])
+def test_small_passes_bf16(opt, windows):
+    """64-row passes in bf16: d = Df = 64, one query head per KV head, more
+    workgroups than the device has CUs."""
+    case = Case(windows, batch=8, Hq=4, Hkv=4, d=64, Df=64, dtype=torch.bfloat16, seed=30, **opt)
+    _two_calls(case, [65, 129, 64, 1, 100, 30, 0, 70], [33, 64, 70, 65, 1, 90, 129, 0], 64, True, f"{opt}", steps=3)
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
@@ -243,22 +289,6 @@ def test_rows_per_pass_many_workgroups(dtype):
     _prefill_from_empty(case, [161, 95, 130, 200], label="many workgroups")
 
 
-def _least_workspace(case, T):
-    """The least workspace size that prefill accepts for T tokens (its NULL
-    pointer is looked at after the size: -1 and no HIP call where it is enough)."""
-    def ok(n):
-        P = ctypes.c_void_p(4096)
-        cu = (ctypes.c_int32 * (case.B + 1))(*([0] * case.B + [T]))
-        return case.g.lib.glide_prefill(ctypes.byref(case.g.cfg), ctypes.c_void_p(256), case.g.state_bytes(), 0, case.L,
-                                        P, P, P, P, None, cu, T, 0, P, None, n, None) == -1
-    lo, hi = 0, case.g.workspace_bytes(T)
-    assert ok(hi) and not ok(lo)
-    while hi - lo > 1:
-        mid = (lo + hi) // 2
-        lo, hi = (lo, mid) if ok(mid) else (mid, hi)
-    return hi
-
-
 @pytest.mark.parametrize("size", ["least", "own", "larger"])
 @pytest.mark.parametrize("windows", [[64], [0, 70]])
 def test_workspace_of_another_size(windows, size):
@@ -267,7 +297,7 @@ def test_workspace_of_another_size(windows, size):
     tokens."""
     case = Case(windows, batch=1, Hq=4, Hkv=4, d=64, Df=64, dtype=torch.float32, seed=26)
     T = 500
-    n = {"least": _least_workspace(case, T), "own": case.g.workspace_bytes(T), "larger": case.g.workspace_bytes(4 * T)}[size]
+    n = {"least": case.least_workspace(T), "own": case.g.workspace_bytes(T), "larger": case.g.workspace_bytes(4 * T)}[size]
     assert size != "least" or n < case.g.workspace_bytes(T)
     q, k, v = case.tokens(T)
     st = case.new_state()
