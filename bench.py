@@ -197,8 +197,8 @@ class Run:
                "algorithmic_bytes_per_launch": dec_bytes,
                "bytes_if_state_written_every_step": decode_bytes(wl, state_write=1),
                "avg_launch_us": dec_step_s * 1e6}
-        mfma = {"bound": "mfma", "kernel": "glide_prefill over the stack (prefill_main + segsum/scan/ringfill/"
-                                          "advance/gather per layer batch)",
+        mfma = {"bound": "mfma", "kernel": "glide_prefill over the stack (prefill_main + begin/segsum/scan/end "
+                                          "per layer batch)",
                 "achieved": pre_flops / (pre_ms * 1e-3) / 1e12, "peak": mfma_peak / 1e12, "unit": "TFLOP/s",
                 "frac": pre_flops / (pre_ms * 1e-3) / mfma_peak,
                 "traffic": traffic and traffic["prefill_call_bytes"],

@@ -712,7 +712,7 @@ constexpr int kMinSegTokens = 64;
 // across layers of different windows), at most kMaxSegChunks chunks walked in
 // order by one workgroup; about 128 tokens in a smaller call.
 constexpr int kSegRounds = 8;
-constexpr int kSegCus = 256;
+constexpr int kSegCus = 256;  // MI355X
 constexpr int kMaxSegChunks = 16;
 inline int32_t min_segment_chunks(int32_t chunk) { return (2 * kMinSegTokens + chunk - 1) / chunk; }
 inline int32_t segment_chunks(int64_t T, int Hkv, int32_t chunk, int32_t nl) {

@@ -18,8 +18,8 @@
 //   scan     exclusive prefix over segments on top of the incoming state;
 //            its end is the new S, z;
 //   main     per (segment, KV head): the segment's chunks in order, S_c kept
-//            in LDS in fp32.  Per pass of 256 query rows: first the banded
-//            window attention over LDS-staged key tiles on MFMA (online
+//            in LDS in fp32.  Per pass of 64, 128 or 256 query rows: first the
+//            banded window attention over LDS-staged key tiles on MFMA (online
 //            softmax, running max m per row); then the linear part, phi(q) on
 //            MFMA, the read-out phi(Q)S_c, phi(q).z_c and the masked block of
 //            the chunk's delayed keys (whose phi(k) is computed once and also
@@ -47,7 +47,6 @@ namespace glide {
 namespace {
 
 constexpr int kThreads = 256;  // helper kernels
-constexpr int kWaves = 4;
 constexpr float kLog2e = 1.4426950408889634f;
 
 // Rows of one (sequence, KV head) of a layer: new tokens come from the
@@ -299,7 +298,7 @@ __device__ __forceinline__ void phi_slab(const WfCols<T, D, DF, kLds>& wf, const
   static_assert(per >= 1 && per * NW == (NK / 16) * FT, "phi tiles must spread evenly over the waves");
   if constexpr (PHI == GLIDE_PHI_SOFTMAX) {
     // The softmax map needs each key row's max and sum over all DF features;
-    // the row's feature tiles are spread over WPK = FT / per waves (per <= 4
+    // the row's feature tiles are spread over WPK = FT / per waves (per <= 8
     // tiles each, one key tile per wave).  Each wave reduces its part (its
     // lanes, then the row's 4 lane groups), the parts meet in the 16 spare
     // elements at the end of the row, two barriers apart.
@@ -503,11 +502,11 @@ struct SegLds {
   static constexpr size_t bytes = (size_t(D) * WROW + size_t(kSegSlab) * (PROW + VROW)) * sizeof(T);
 };
 
-// bf16: 128 registers at most, so that two workgroups share a CU (their LDS is
-// 74 KB each at D = 128): one computes while the other waits at a barrier or
-// for its slab (this kernel: 198 -> 173 us over 4 x 32K tokens,
-// 308 -> 266 us over the batch-1 stack).  fp32:
-// the LDS admits one workgroup.
+// bf16: 128 registers at most (three spilled by ELU + 1 at D = DF = 128, none
+// elsewhere), so that two workgroups share a CU (their LDS is 74 KB each at
+// D = 128): one computes while the other waits at a barrier or for its slab
+// (this kernel: 198 -> 173 us over 4 x 32K tokens, 308 -> 266 us over the
+// batch-1 stack).  fp32: the LDS admits one workgroup.
 template <typename T, int D, int DF, int PHI>
 __global__ __launch_bounds__(kSegThreads)
 __attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 ? 4 : 2, sizeof(T) == 2 ? 4 : 2)))
@@ -707,8 +706,8 @@ __global__ __launch_bounds__(kThreads) void prefill_scan(PrefillArgs a) {
 //
 // Accumulators are kept transposed (O^T = V^T P^T): a lane holds 4
 // consecutive output columns of one query row, so the online-softmax rescale
-// and the final normalisation are lane-local and the output leaves in 8-byte
-// (bf16) stores.
+// and the final normalisation are lane-local; the output leaves in 16-byte
+// stores (store_row).
 //
 // The walk is software-pipelined over passes (RB query rows of a chunk):
 // the next pass's query rows, first slab of delayed keys and first band tile
@@ -722,10 +721,10 @@ __global__ __launch_bounds__(kThreads) void prefill_scan(PrefillArgs a) {
 // workgroup per CU.  RB is 256 on 8 waves (two q-tiles each) where a chunk has
 // that many rows (C tokens x G heads); a chunk of at most 128 rows takes 128
 // on 8 waves, and one of at most 64 rows may take 64 on 4 (one q-tile each;
-// layer_t chooses): every wave carries its
-// q-tiles' matrix work whether their rows exist or not, so the larger pass
-// multiplies mostly padding (C = 64, G = 1: three quarters of it; 512 tokens
-// x 4 heads, d = 64, fp32: 104 us per call in 256-row passes, 60 us in 64-row ones).
+// layer_t chooses): every wave carries its q-tiles' matrix work whether their
+// rows exist or not, so the larger pass multiplies mostly padding (C = 64,
+// G = 1: three quarters of it; 512 tokens x 4 heads, d = 64, fp32: 104 us per
+// call in 256-row passes, 60 us in 64-row ones).
 template <typename T, int D, int DF>
 struct MainLds {
   static constexpr int NBUF = 2;  // band stages
@@ -1719,13 +1718,13 @@ void prefill_main(PrefillArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// ringfill: tokens [max(p0, p_end - W), p_end) into their ring slots.  A key
+// end: tokens [max(p0, p_end - W), p_end) into their ring slots.  A key
 // slot takes 16-byte chunks (8 consecutive columns); the value layout keeps 8
 // consecutive slots of one column together, so a thread gathers one column of
 // 8 consecutive tokens (R is a multiple of 8, so such a group never wraps)
 // and stores it at once, or element by element where the group is only partly
 // in range (its other slots may hold live tokens).
-// Then advance: pos += T_b; the scan left S, z = the sums over tokens
+// Then pos += T_b; the scan left S, z = the sums over tokens
 // [0, max(0, pos - Wd)), nothing pending.  Every workgroup of a unit reads the
 // old pos, so the last of them to finish writes the new one: each waits for
 // its own reads, then adds one to the unit's count (cleared by `begin`, which
