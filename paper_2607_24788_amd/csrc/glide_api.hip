@@ -217,23 +217,37 @@ size_t prefill_need(const glide_config* c, int64_t T) {
 }
 
 // Tokens of a prefill call's short segments where they are expected to end
-// sooner than the least that segment_chunks gives; 0: not short.
-int32_t short_segment_tokens(const glide_config* c, int32_t layer0, int32_t n_layers, const int32_t* cu, int32_t chunk,
-                             int32_t per_launch) {
+// sooner than the least that segment_chunks gives (which the call would take);
+// 0: not short.  `windows`: of
+// one launch's layers, the longest first.  A window counts as no longer than the
+// call's longest sequence (the positions are on the device: a fresh prompt's
+// windows are not full).
+int32_t short_segment_tokens(const glide_config* c, const std::vector<int32_t>& windows, const int32_t* cu,
+                             int32_t chunk) {
   const int32_t n_half = (kMinSegTokens + chunk - 1) / chunk, n = min_segment_chunks(chunk);
-  if (n_half >= n || segment_chunks(cu[c->batch], c->n_kv_heads, chunk, per_launch) != n) return 0;
-  auto workgroups = [&](int32_t chunks) {
+  if (n_half >= n) return 0;
+  int32_t longest = 0;
+  for (int32_t b = 0; b < c->batch; ++b) longest = std::max(longest, cu[b + 1] - cu[b]);
+  auto workgroups = [&](int32_t chunks) {  // of one layer
     int64_t segs = 0;
     for (int32_t b = 0; b < c->batch; ++b) segs += (cu[b + 1] - cu[b] + chunks * chunk - 1) / (chunks * chunk);
-    return segs * c->n_kv_heads * per_launch;
+    return segs * c->n_kv_heads;
+  };
+  auto us = [&](int64_t wgs, int32_t chunks) {
+    double work = 0, rounds = 0;
+    int64_t first = 0;  // workgroups of the layers so far
+    for (int32_t W : windows) {
+      const double t = segment_us(chunks, chunk, c->n_q_heads / c->n_kv_heads, std::min(W, longest), c->head_dim,
+                                  c->dtype == GLIDE_F32);
+      work += double(wgs) * t;
+      first += wgs;
+      rounds = std::max(rounds, double((first + kSegCus - 1) / kSegCus) * t);
+    }
+    return std::max(work / kSegCus, rounds) + 0.03 * double(first);
   };
   const int64_t wgs = workgroups(n_half);
-  if (wgs > kShortWgs) return 0;
-  double chunk_us = 0;  // mean over the layers
-  for (int32_t l = layer0; l < layer0 + n_layers; ++l)
-    chunk_us += prefill_chunk_us(chunk, c->n_q_heads / c->n_kv_heads, c->windows[l], c->head_dim,
-                                 c->dtype == GLIDE_F32) / n_layers;
-  return segments_us(wgs, n_half, chunk_us) < segments_us(workgroups(n), n, chunk_us) ? n_half * chunk : 0;
+  if (wgs * int64_t(windows.size()) > kShortWgs) return 0;
+  return us(wgs, n_half) < us(workgroups(n), n) ? n_half * chunk : 0;
 }
 
 // Decode-style launch descriptor of layers [layer0, layer0 + n): per launch
@@ -493,9 +507,21 @@ glide_status glide_prefill(const glide_config* cfg, void* state, size_t state_by
   // that many layers) as the caller's workspace holds
   auto slot_of = [&](int32_t nl) { return prefill_ws(cfg, T, nl).slot; };
   const int32_t per_launch = std::max(1, prefill_layers_per_launch(n_layers, workspace_bytes, slot_of));
+  // Layers by decreasing window, dealt round-robin over the launches: every
+  // launch gets a like mix of long and short windows, longest first (their
+  // workgroups are dispatched first).
+  std::vector<int32_t> rank(n_layers);
+  for (int32_t j = 0; j < n_layers; ++j) rank[j] = j;
+  std::stable_sort(rank.begin(), rank.end(), [&](int32_t x, int32_t y) {
+    return cfg->windows[layer0 + x] > cfg->windows[layer0 + y];
+  });
+  const int32_t n_launch = (n_layers + per_launch - 1) / per_launch;
   PrefillWorkspace w = prefill_ws(cfg, T, per_launch);
   int32_t seg_len = chunk * segment_chunks(T, Hkv, chunk, per_launch);
-  const int32_t half = short_segment_tokens(cfg, layer0, n_layers, cu_seqlens_host, chunk, per_launch);
+  std::vector<int32_t> windows;  // of the first launch
+  for (int32_t j = 0; j < n_layers; j += n_launch) windows.push_back(cfg->windows[layer0 + rank[j]]);
+  const int32_t half = seg_len == chunk * min_segment_chunks(chunk)
+                           ? short_segment_tokens(cfg, windows, cu_seqlens_host, chunk) : 0;
   if (half > 0) {
     const PrefillWorkspace ws = prefill_ws_of(cfg, T, T / half);
     if (size_t(per_launch) * ws.slot <= workspace_bytes) {
@@ -556,15 +582,6 @@ glide_status glide_prefill(const glide_config* cfg, void* state, size_t state_by
     return nseg;
   };
 
-  // Layers by decreasing window, dealt round-robin over the launches: every
-  // launch gets a like mix of long and short windows, longest first (their
-  // workgroups are dispatched first).
-  std::vector<int32_t> rank(n_layers);
-  for (int32_t j = 0; j < n_layers; ++j) rank[j] = j;
-  std::stable_sort(rank.begin(), rank.end(), [&](int32_t x, int32_t y) {
-    return cfg->windows[layer0 + x] > cfg->windows[layer0 + y];
-  });
-  const int32_t n_launch = (n_layers + per_launch - 1) / per_launch;
   for (int32_t li = 0; li < n_launch; ++li) {
     std::vector<int32_t> order;
     for (int32_t j = li; j < n_layers; j += n_launch) order.push_back(rank[j]);

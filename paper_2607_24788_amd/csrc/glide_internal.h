@@ -724,26 +724,26 @@ inline int32_t segment_chunks(int64_t T, int Hkv, int32_t chunk, int32_t nl) {
 
 // Short segments, half as many chunks (never under kMinSegTokens tokens), where
 // segment_chunks gives its least and they end sooner by a model of the call in
-// microseconds: rounds of one workgroup per CU, each a start and its chunks
-// (below), and 0.03 per segment and head for the records.  Fitted to 2073
-// calls of 128 .. 16000 tokens timed both ways (fresh and continuing; d = 64
-// and 128; 1, 4 and 8 query heads per KV head; fp32 and bf16; W = 0 .. 4096):
-// on average 0.7% over the better of the two, and at most 2.8% over the longer
-// segments; always the longer ones: 14% over.  512 tokens x 4 heads (fp32,
-// W = 64), one round of one chunk in place of two: 60 -> 41.7 us per call;
-// 10000 tokens x 8 heads, five rounds of one or three of two: W = 0 161 / 129
-// us, W = 2048 482 / 522 us.  A call takes them only up to kShortWgs workgroups
-// (what the reported workspace has room for) and where the records fit the
-// workspace it was given.
+// microseconds.  A workgroup of the main kernel is a start of 8 and its chunks;
+// a launch hands them to the CUs layer by layer, the longest windows first, and
+// ends no sooner than its work spread over the CUs, nor than the rounds of one
+// workgroup per CU that any first few layers need; a record costs 0.03.
+// Against both ways timed (fresh and continuing calls; d = 64 and 128; 1, 4 and 8
+// query heads per KV head; fp32 and bf16), over the better of the two on average:
+// 2073 calls of one layer, 128 .. 16000 tokens, 0.7% (always the longer ones: 14%);
+// 3744 calls of 2 .. 32 layers, 0.8% (always the longer ones: 15%).  512 tokens x
+// 4 heads (fp32, W = 64), one round of one chunk in place of two: 60 -> 41.7 us
+// per call; 10000 tokens x 8 heads, five rounds of one or three of two: W = 0
+// 161 / 129 us, W = 2048 482 / 522 us.  A call takes them only up to kShortWgs
+// workgroups (what the reported workspace has room for) and where the records
+// fit the workspace it was given.
 constexpr int kShortWgs = 9 * kSegCus;
-inline double segments_us(int64_t wgs, int32_t chunks, double chunk_us) {
-  return double((wgs + kSegCus - 1) / kSegCus) * (8 + chunks * chunk_us) + 0.03 * double(wgs);
-}
-// One chunk of C tokens x G heads in a layer of window W: per pass of 256 rows
-// the linear part, the band's fixed part and a microsecond per 32 keys.
-inline double prefill_chunk_us(int32_t C, int32_t G, int32_t W, int d, bool fp32) {
+// A workgroup over `chunks` chunks of C tokens x G heads in a layer of window W:
+// per chunk and pass of 256 rows the linear part, the band's fixed part and a
+// microsecond per 32 keys.
+inline double segment_us(int32_t chunks, int32_t C, int32_t G, int32_t W, int d, bool fp32) {
   const double us = double((C * G + 255) / 256) * (8 + (W > 0 ? 4 : 0) + W / 32.0);
-  return us * (fp32 ? 4 : 1) / (d == 64 ? 3 : 1);
+  return 8 + chunks * us * (fp32 ? 4 : 1) / (d == 64 ? 3 : 1);
 }
 
 // Segments of a call of T tokens (beyond one per sequence), at most: the
