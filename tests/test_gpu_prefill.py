@@ -307,31 +307,32 @@ def test_workspace_of_another_size(windows, size):
     case.check_state(st, k, v, [T], f"workspace {size}")
 
 
-@pytest.mark.parametrize("lens,W,d,tokens", [
-    ([512], 0, 128, 64),              # one round of workgroups either way
-    ([10000], 0, 128, 128),           # five rounds of one chunk or three of two: the starts weigh more
-    ([10000], 2048, 128, 64),         # the chunks weigh more
-    ([10000], 0, 64, 128),
-    ([33 + 8 * i for i in range(32)], 0, 128, 128),  # by T alone three rounds, with every sequence's ends four
+@pytest.mark.parametrize("lens,windows,d,tokens", [
+    ([512], [0], 128, 64),            # one round of workgroups either way
+    ([10000], [0], 128, 128),         # five rounds of one chunk or three of two: the starts weigh more
+    ([10000], [2048], 128, 64),       # the chunks weigh more
+    ([10000], [0], 64, 128),
+    ([33 + 8 * i for i in range(32)], [0], 128, 128),  # by T alone three rounds, with every sequence's ends three or two
+    ([1500], [64, 4096], 128, 64),    # one round of the longer window's workgroups either way
+    ([2500], [64, 4096], 128, 128),   # two rounds of them or one
 ])
-def test_segment_tokens(lens, W, d, tokens):
-    """The segments of a call (8 KV heads, bf16) as its records in the
-    workspace show them: short ones only where they are expected to end sooner."""
-    case = Case([W], batch=len(lens), Hq=32, Hkv=8, d=d, Df=d, dtype=torch.bfloat16, seed=27)
+def test_segment_tokens(lens, windows, d, tokens):
+    """The segments of a call from empty (8 KV heads, bf16), as its records in
+    the workspace show them (nothing else is written there): short ones only
+    where they are expected to end sooner."""
+    L = len(windows)
+    case = Case(windows, batch=len(lens), Hq=32, Hkv=8, d=d, Df=d, dtype=torch.bfloat16, seed=27)
     T, g = sum(lens), case.g
     gen = torch.Generator(device="cuda").manual_seed(27)
-    x = lambda h: (torch.randn((1, T, h, d), generator=gen, device="cuda") * d ** -0.5).to(torch.bfloat16)  # noqa: E731
-    q, out = x(32), torch.empty((1, T, 32, d), dtype=torch.bfloat16, device="cuda")
+    x = lambda h: (torch.randn((L, T, h, d), generator=gen, device="cuda") * d ** -0.5).to(torch.bfloat16)  # noqa: E731
+    q, out = x(32), torch.empty((L, T, 32, d), dtype=torch.bfloat16, device="cuda")
     ws = torch.full((g.workspace_bytes(T),), 0xff, dtype=torch.uint8, device="cuda")
     cu = [0]
     for n in lens:
         cu.append(cu[-1] + n)
     g.prefill(case.new_state(), case.phi_w.cuda(), q, x(8), x(8), cu, out, ws)
-    start = 2 * (len(lens) * 8 * W * d * 2)  # behind the history keys and values
-    rec = 8 * (d * d + d) * 4
-    n = (ws.numel() - start) // rec
-    written = (ws[start:start + n * rec].view(n, rec) != 0xff).any(1)
-    assert int(written.sum()) == sum(-(-x // tokens) for x in lens)
+    words = int((ws.view(torch.int32) != -1).sum())
+    assert words == L * sum(-(-n // tokens) for n in lens) * 8 * (d * d + d)
 
 
 @pytest.mark.parametrize("windows", [[70], [0, 70], [0]])
