@@ -314,7 +314,7 @@ def test_workspace_of_another_size(windows, size):
     ([10000], [0], 64, 128),
     ([33 + 8 * i for i in range(32)], [0], 128, 128),  # by T alone three rounds, with every sequence's ends three or two
     ([1500], [64, 4096], 128, 64),    # one round of the longer window's workgroups either way
-    ([2500], [64, 4096], 128, 128),   # two rounds of them or one
+    ([3500], [16, 2048], 128, 128),   # two rounds of them or one
 ])
 def test_segment_tokens(lens, windows, d, tokens):
     """The segments of a call from empty (8 KV heads, bf16), as its records in
